@@ -1,20 +1,19 @@
-// GEMM C = epi(A B^T) on MFMA for gfx950.
+// GEMM C = epi(A B^T) on MFMA for gfx950: the kernel of the large bf16
+// problems, and the dispatch to it and to gemm_ring.h's tile shapes.
 //
 // Both operands are K-contiguous (nn.Linear layout), which is exactly the
 // per-lane layout the MFMA operands want: every lane feeds a 16-byte run of
-// consecutive k. Workgroup tile 256 x 256 (128 x 128 for small problems),
-// k-tile 128 bytes per row (64 bf16 / 32 f32), split over a grid of waves
-// that each own a block of 32x32 output blocks (bf16: four 16x16x32 MFMA
-// tiles each; f32: one 32x32x2 tile). Operand tiles are copied
-// global -> LDS by buffer loads that write LDS directly (no staging
-// registers, no LDS store instructions), double-buffered (2 x 64 KB of the
-// 160 KB LDS at 256 x 256): tile kt+1 is requested while tile kt is
-// computed. The 16-byte chunks of each row are XOR-swizzled (swz) so the
-// 32-row fragment reads are bank-conflict free; each lane fetches the chunk
-// that the swizzle places in the LDS slot its load writes. Ragged M and N:
-// rows past the matrix read as zero through the descriptor bounds and
-// stores are predicated; K must be a multiple of the k-tile (the plan pads
-// pruned widths to 64).
+// consecutive k. Workgroup tile 256 x 256, k-tile 128 bytes per row (64 bf16),
+// split over a grid of waves that each own a block of 32x32 output blocks (four
+// 16x16x32 MFMA tiles each). Operand tiles are copied global -> LDS by buffer
+// loads that write LDS directly (no staging registers, no LDS store
+// instructions), double-buffered (2 x 64 KB of the 160 KB LDS): tile kt+1 is
+// requested while tile kt is computed. The 16-byte chunks of each row are
+// XOR-swizzled (swz) so the fragment reads are bank-conflict free; each lane
+// fetches the chunk that the swizzle places in the LDS slot its load writes.
+// Ragged M and N: rows past the matrix read as zero through the descriptor
+// bounds and stores are predicated; K must be a multiple of the k-tile (the
+// plan pads pruned widths to 64).
 //
 // Index-table gather (the step's active parameters read in place from the
 // union weight set, no compacted copy):
@@ -23,117 +22,37 @@
 //            channels are dropped from the output width.
 //   GA_KCH   16-byte K chunk c of every B row is read from chunk kch[c] of
 //            that row (-1: zeros).  Used where dropped heads or FFN chunks
-//            shorten the reduction.  The chunk table is staged in LDS once.
+//            shorten the reduction.  This kernel stages the chunk table in LDS once.
 // Masked rows / chunks get an offset past the descriptor's range, which the
 // buffer load returns as zero.
 #include <type_traits>
 
-#include "common.h"
-#include "kernels.h"
+#include "gemm_ring.h"
 
 namespace dif {
-// Fragment k of a k-step in the order its MFMAs first use them (MFMA i
-// multiplies A row block i / TN by B column block i % TN): the value is a
-// row block index (< TM) or TM + a column block index.  For 4 x 2 blocks:
-// A0 B0 B1 A1 A2 A3.
-// (a table built at compile time: indexing it with an unrolled loop's
-// counter gives constants, so the fragment arrays stay in registers)
-template <int TM, int TN>
-struct FirstUse {
-  int v[TM + TN];
-};
-template <int TM, int TN>
-__host__ __device__ constexpr FirstUse<TM, TN> first_use_table() {
-  FirstUse<TM, TN> t{};
-  bool seen[TM + TN] = {};
-  int n = 0;
-  for (int i = 0; i < TM * TN; ++i) {
-    const int a = i / TN, b = TM + i % TN;
-    if (!seen[a]) {
-      seen[a] = true;
-      t.v[n++] = a;
-    }
-    if (!seen[b]) {
-      seen[b] = true;
-      t.v[n++] = b;
-    }
-  }
-  return t;
-}
 
-constexpr int G_BKC = 8;    // 16-byte chunks per k-tile row (128 bytes)
-constexpr int BN_MAX = 256; // largest workgroup tile width over the shapes below
+constexpr int BN_MAX = 256; // widest workgroup tile
 
-enum { GA_NONE = 0, GA_ROWS = 1, GA_KCH = 2 };
-constexpr uint32_t kMasked = 0x80000000u;  // buffer offset beyond any descriptor range
-
-// Up to three B matrices ("segments", e.g. the q, k and v weights) share A
-// and one launch; segment s writes output columns [s*N, (s+1)*N).
-constexpr int kMaxSeg = 3;
-
-template <typename T, typename OutT>
-struct GemmParams {
-  const T* A;
-  const T* Bs[kMaxSeg];
-  OutT* C;
-  int64_t lda, ldb, ldc;
-  int M, N, K;
-  const float* biases[kMaxSeg];
-  int nseg;
-  const float* gate0;
-  const float* gate1;
-  const int32_t* rows;   // GA_ROWS
-  const int32_t* kch;    // GA_KCH
-  int b_rows;            // GA_ROWS: rows of the union B matrix
-  int vec4;              // C rows allow aligned 4-element accesses
-  // transposed output: columns from output column vt_col0 on go to
-  // vt[(b * vt_dims + col - vt_col0) * ldvt + j] for row m = b * vt_L + j
-  OutT* vt;
-  int64_t ldvt;
-  int vt_col0, vt_dims, vt_L;
-  int vt_vec4;           // vt rows allow aligned 4-element stores and vt_L % 4 == 0
-};
-
-// four consecutive output elements: 8-byte (bf16) or 16-byte (f32) accesses
-__device__ __forceinline__ void load4(const bf16* p, float* v) {
-  const bf16x4 x = *reinterpret_cast<const bf16x4*>(p);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = (float)x[e];
-}
-__device__ __forceinline__ void load4(const float* p, float* v) {
-  const f32x4 x = *reinterpret_cast<const f32x4*>(p);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = x[e];
-}
-__device__ __forceinline__ void store4(bf16* p, const float* v) {
-  bf16x4 x;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) x[e] = (bf16)v[e];
-  *reinterpret_cast<bf16x4*>(p) = x;
-}
-__device__ __forceinline__ void store4(float* p, const float* v) {
-  f32x4 x;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) x[e] = v[e];
-  *reinterpret_cast<f32x4*>(p) = x;
-}
-
-// WGM x WGN waves; each wave owns TM x TN 32x32 output blocks; two LDS stages
-// of BKC 16-byte chunks per operand row.
-template <typename T, typename OutT, int EPI, int GA, int WGM, int WGN, int TM, int TN, int BKC>
-__global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kernel(GemmParams<T, OutT> p) {
+// 256 x 256 workgroup tile as 8 waves (2 x 4) of 128 x 64: each wave owns
+// TM x TN 32x32 output blocks; two LDS stages of BKC 16-byte chunks per operand
+// row.
+template <typename OutT, int EPI, int GA>
+__global__ __launch_bounds__(512, 1) void gemm_nt_kernel(GemmParams<bf16, OutT> p) {
+  using T = bf16;
+  static_assert(GA == GA_NONE || GA == GA_KCH, "row-gathered B runs gemm_ring.h");
+  constexpr int WGM = 2, WGN = 4, TM = 4, TN = 2, BKC = G_BKC;
   constexpr int NW = WGM * WGN;
   constexpr int NT = 64 * NW;
   constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32;
   constexpr int VEC = Chunk<T>::VEC;
   constexpr int BK = BKC * VEC;
   constexpr int RPI = 64 / BKC;           // rows filled by one wave load instruction (1 KB)
-  // Eight waves: waves 0..3, the older wave of each SIMD pair, issue all of
+  // Waves 0..3, the older wave of each SIMD pair, issue all of
   // a tile's loads.  The older wave wins the SIMD's issue arbitration and
   // finishes its share of a k-tile first; the loads' issue time then comes
   // off the younger wave, which ends each k-tile (measured 4.7% on the
   // step's five projection shapes).
-  constexpr int NLW = NW == 8 ? 4 : NW;   // loading waves
+  constexpr int NLW = 4;                  // loading waves
   constexpr int LA = BM / (RPI * NLW), LB = BN / (RPI * NLW);
   constexpr int LPT = LA + LB;            // loads per thread per k-tile
   static_assert(LA * RPI * NLW == BM && LB * RPI * NLW == BN, "staging split");
@@ -144,29 +63,18 @@ __global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kerne
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
   const int g = lane >> 5, col = lane & 31;
-  // bf16: each 32 x 32 block of the wave is four 16 x 16 MFMA tiles
+  // Each 32 x 32 block of the wave is four 16 x 16 MFMA tiles
   // (v_mfma_f32_16x16x32_bf16, k 32 per instruction): at the same operand
   // bytes per flop it draws less power than the 32 x 32 x 16 form, and the
   // chip holds a higher clock under it (2.03 against 1.75 PFLOP/s sustained
   // with every CU issuing nothing else; here 1.83-2.04 against 1.57-1.71
   // GHz, +1 % per step: the tile loads, not the matrix units, bound the
-  // k-loop).  float32 keeps 32 x 32 x 2, and so does the row-gathered B
-  // (its eight per-instruction row offsets would not fit beside the
-  // 16 x 16 schedule's registers).
-  constexpr bool M16 = std::is_same<T, bf16>::value && GA != GA_ROWS;
+  // k-loop).
 
-  // logical tile: XCD-contiguous ranges, then groups of GM row-tiles that
-  // walk the N tiles of all segments together (operand reuse in L2)
   const int nbm = (p.M + BM - 1) / BM, nbn = (p.N + BN - 1) / BN;
-  const int nbv = nbn * p.nseg;
-  const int bid = xcd_remap(blockIdx.x, nbm * nbv);
-  constexpr int GM = 8;
-  const int group = bid / (GM * nbv);
-  const int first_m = group * GM;
-  const int gsize = min(nbm - first_m, GM);
-  const int in_group = bid - group * GM * nbv;
-  const int m0 = (first_m + in_group % gsize) * BM;
-  const int nt = in_group / gsize;
+  int mt, nt;
+  tile_of(blockIdx.x, nbm, nbn * p.nseg, mt, nt);
+  const int m0 = mt * BM;
   const int sg = nt / nbn;
   const int n0 = (nt - sg * nbn) * BN;
   const T* Bsg = p.Bs[sg];
@@ -178,21 +86,16 @@ __global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kerne
   // zero.
   constexpr uint32_t kRsrcWord3 = 0x00020000u;
   const uint32_t a_bytes = (uint32_t)(min(BM, p.M - m0) * p.lda * (int64_t)sizeof(T));
-  // GA_ROWS: one descriptor over the whole union matrix, rows picked per thread
-  const uint32_t b_bytes =
-      GA == GA_ROWS ? (uint32_t)((int64_t)p.b_rows * p.ldb * (int64_t)sizeof(T))
-                    : (uint32_t)(min(BN, p.N - n0) * p.ldb * (int64_t)sizeof(T));
-  const T* b_base = GA == GA_ROWS ? Bsg : Bsg + (int64_t)n0 * p.ldb;
+  const uint32_t b_bytes = (uint32_t)(min(BN, p.N - n0) * p.ldb * (int64_t)sizeof(T));
+  const T* b_base = Bsg + (int64_t)n0 * p.ldb;
   const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<T*>(p.A + (int64_t)m0 * p.lda), (short)0, a_bytes, kRsrcWord3);
   const __amdgpu_buffer_rsrc_t b_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(b_base), (short)0, b_bytes, kRsrcWord3);
   // lane offsets of load instruction i: the first one's plus i times a
   // row stride, added when the load issues (kept whole in the vector offset,
-  // which the descriptor's range check covers), except for gathered B rows,
-  // which need one per instruction
-  constexpr int LBV = GA == GA_ROWS ? LB : 1;
-  uint32_t a_off[1], b_off[LBV];
+  // which the descriptor's range check covers)
+  uint32_t a_off, b_off;
   const uint32_t a_step = (uint32_t)(NLW * RPI * p.lda * (int64_t)sizeof(T));
   const uint32_t b_step = (uint32_t)(NLW * RPI * p.ldb * (int64_t)sizeof(T));
   // direct-to-LDS: instruction i of loading wave lw fills LDS rows
@@ -206,19 +109,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kerne
   const bool loader = wave < NLW;
   auto drow = [&](int i) { return (i * NLW + lw) * RPI + lane / BKC; };
   const int dchunk = swz<BKC>(drow(0), lane % BKC);
-  a_off[0] = (uint32_t)((drow(0) * p.lda + dchunk * VEC) * (int64_t)sizeof(T));
-#pragma unroll
-  for (int i = 0; i < LBV; ++i) {
-    if constexpr (GA == GA_ROWS) {
-      const int n = n0 + drow(i);
-      const int r = n < p.N ? p.rows[n] : -1;
-      b_off[i] = r >= 0 ? (uint32_t)((r * p.ldb + dchunk * VEC) * (int64_t)sizeof(T)) : kMasked;
-    } else if constexpr (GA == GA_KCH) {
-      b_off[i] = (uint32_t)(drow(i) * p.ldb * (int64_t)sizeof(T));
-    } else {
-      b_off[i] = (uint32_t)((drow(i) * p.ldb + dchunk * VEC) * (int64_t)sizeof(T));
-    }
-  }
+  a_off = (uint32_t)((drow(0) * p.lda + dchunk * VEC) * (int64_t)sizeof(T));
+  b_off = (uint32_t)((drow(0) * p.ldb + (GA == GA_KCH ? 0 : dchunk * VEC)) * (int64_t)sizeof(T));
   const int nk = p.K / BK;
   if constexpr (GA == GA_KCH) {
     for (int c = tid; c < p.K / VEC; c += NT) {
@@ -244,7 +136,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kerne
     const int koff = kt * BK * (int)sizeof(T);
     // (opaque copies: the per-instruction offsets are formed here, not
     // hoisted out of the k-loop into registers of their own)
-    uint32_t a0 = a_off[0], b0 = b_off[0];
+    uint32_t a0 = a_off, b0 = b_off;
     asm volatile("" : "+v"(a0), "+v"(b0));
     if (u < LA) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_t*)&smem[st][(u * NLW + lw_s) * RPI][0],
@@ -254,8 +146,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kerne
       lds_t* dst = (lds_t*)&smem[st][BM + (i * NLW + lw_s) * RPI][0];
       if constexpr (GA == GA_KCH)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, b0 + i * b_step + kb, 0, 0, 0);
-      else if constexpr (GA == GA_ROWS)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, b_off[i], koff, 0, 0);
       else
         __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, b0 + i * b_step, koff, 0, 0);
     }
@@ -267,39 +157,28 @@ __global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kerne
       if (loader) issue_one(kt, u, std::integral_constant<int, 0>{});
   };
 
-  // accumulators: 32 x 32 blocks (float32) or 16 x 16 tiles (bf16), the same
-  // 16 registers per 32 x 32 block either way
-  constexpr int AM = M16 ? 2 * TM : TM, AN = M16 ? 2 * TN : TN;
-  typedef typename std::conditional<M16, f32x4, f32x16>::type AccT;
-  constexpr int AR = M16 ? 4 : 16;
-  AccT acc[AM][AN];
+  // accumulators: 16 x 16 tiles, 16 registers per 32 x 32 block
+  constexpr int AM = 2 * TM, AN = 2 * TN;
+  f32x4 acc[AM][AN];
 #pragma unroll
   for (int i = 0; i < AM; ++i)
 #pragma unroll
-    for (int j = 0; j < AN; ++j)
-#pragma unroll
-      for (int r = 0; r < AR; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < AN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // MFMA operand fragments, double-buffered in registers: the fragments of
-  // k-step ks+1 are read while the MFMAs of k-step ks issue, one read after
-  // each MFMA, in the order k-step ks+1's MFMAs first use them.  Scheduling
-  // barriers keep that order (left alone, the compiler sinks every read next
-  // to its first use).
-  // k-steps per k-tile: 16 k (32 x 32 x 16) or 32 k (16 x 16 x 32) each
-  constexpr int KSN = M16 ? BKC / 4 : BKC / 2;
-  static_assert(KSN % 2 == 0, "fragment slots alternate");
-  // fragments: rows of 32 (lane % 32, chunk 2 ks + lane / 32) or of 16
-  // (lane % 16, chunk 4 ks + lane / 16)
-  constexpr int FR = M16 ? 16 : 32;
-  u32x4 fa[M16 ? 1 : 2][AM], fb[M16 ? 1 : 2][AN];
-  const int frow = M16 ? (lane & 15) : col;
+  // MFMA operand fragments (rows of 16: lane % 16, chunk 4 ks + lane / 16),
+  // each read for k-step ks+1 into its own registers right after its last MFMA
+  // of k-step ks.  Scheduling barriers keep that order (left alone, the
+  // compiler sinks every read next to its first use).
+  constexpr int KSN = BKC / 4;   // k-steps (of 32) per k-tile
+  u32x4 fa[AM], fb[AN];
+  const int frow = lane & 15;
   constexpr FirstUse<AM, AN> fu = first_use_table<AM, AN>();
-  // fragment read r (first_use order) of k-step ks of stage st into slot
-  auto frag_one = [&](int st, int ks, int slot, int r) {
-    const int c = M16 ? swz<BKC>(frow, 4 * ks + (lane >> 4)) : swz<BKC>(col, 2 * ks + g);
+  // fragment read r (first_use order) of k-step ks of stage st
+  auto frag_one = [&](int st, int ks, int r) {
+    const int c = swz<BKC>(frow, 4 * ks + (lane >> 4));
     // (rows are frow + multiples of 16, so the swizzle sees frow's bits)
-    if (r < AM) fa[slot][r] = smem[st][wm * TM * 32 + r * FR + frow][c];
-    else fb[slot][r - AM] = smem[st][BM + wn * TN * 32 + (r - AM) * FR + frow][c];
+    if (r < AM) fa[r] = smem[st][wm * TM * 32 + r * 16 + frow][c];
+    else fb[r - AM] = smem[st][BM + wn * TN * 32 + (r - AM) * 16 + frow][c];
   };
   // One k-tile (stage st is compile-time, so fragment and load addresses are
   // constants plus immediate offsets): wait for this wave's loads of tile kt,
@@ -323,52 +202,40 @@ __global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kerne
       for (int u = 0; u < LPT / 2; ++u) issue_one(kt + 1, u, NS{});
     }
 #pragma unroll
-    for (int r = 0; r < AM + AN; ++r) frag_one(st, 0, 0, fu.v[r]);
+    for (int r = 0; r < AM + AN; ++r) frag_one(st, 0, fu.v[r]);
 #pragma unroll
     for (int ks = 0; ks < KSN; ++ks) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < AM * AN; ++i) {
-        if constexpr (M16) {
-          // Two halves over the B fragments (B 0..AN/2-1, then the rest),
-          // each running through every A fragment, so every fragment is
-          // read for the next k-step into its own registers right after its
-          // last MFMA here (one register slot per fragment): the first
-          // half's B after MFMA AM * AN / 2 - 1, A fragment a after its
-          // second-half use, the second half's B after the last MFMA
-          constexpr int HB = AN / 2;
-          const int h = i / (AM * HB), a = (i % (AM * HB)) / HB, b = h * HB + i % HB;
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa[0][a]),
-                                                              __builtin_bit_cast(bf16x8, fb[0][b]),
-                                                              acc[a][b], 0, 0, 0);
-          if (ks + 1 < KSN) {
-            if (i == AM * HB - 1) {
+        // Two halves over the B fragments (B 0..AN/2-1, then the rest),
+        // each running through every A fragment, so every fragment is
+        // read for the next k-step into its own registers right after its
+        // last MFMA here (one register slot per fragment): the first
+        // half's B after MFMA AM * AN / 2 - 1, A fragment a after its
+        // second-half use, the second half's B after the last MFMA
+        constexpr int HB = AN / 2;
+        const int h = i / (AM * HB), a = (i % (AM * HB)) / HB, b = h * HB + i % HB;
+        mma16<T>(acc[a][b], fa[a], fb[b]);
+        if (ks + 1 < KSN) {
+          if (i == AM * HB - 1) {
 #pragma unroll
-              for (int bb = 0; bb < HB; ++bb) frag_one(st, ks + 1, 0, AM + bb);
-            }
-            if (h == 1 && i % HB == HB - 1) frag_one(st, ks + 1, 0, a);
-            if (i == AM * AN - 1) {
-#pragma unroll
-              for (int bb = HB; bb < AN; ++bb) frag_one(st, ks + 1, 0, AM + bb);
-            }
+            for (int bb = 0; bb < HB; ++bb) frag_one(st, ks + 1, AM + bb);
           }
-        } else {
-          Mma<T>::step(acc[i / AN][i % AN], fa[ks & 1][i / AN], fb[ks & 1][i % AN]);
-          if (ks + 1 < KSN && i < AM + AN) frag_one(st, ks + 1, (ks + 1) & 1, fu.v[i]);
+          if (h == 1 && i % HB == HB - 1) frag_one(st, ks + 1, a);
+          if (i == AM * AN - 1) {
+#pragma unroll
+            for (int bb = HB; bb < AN; ++bb) frag_one(st, ks + 1, AM + bb);
+          }
         }
-        // the tile's second half of loads: after the first k-step's MFMAs
-        // (32 x 32 x 16), or after its first eight (16 x 16 x 32: its k-steps
-        // are half as many and the loads want the time to land; after the
-        // whole k-step 3 % slower, all at the barrier 0.8 %)
-        if (M16 && ks == 0 && i == 7 && more && loader) {
+        // the tile's second half of loads: after the first eight MFMAs (the
+        // loads want the time to land; after the whole k-step 3 % slower, all
+        // at the barrier 0.8 %)
+        if (ks == 0 && i == 7 && more && loader) {
 #pragma unroll
           for (int u = LPT / 2; u < LPT; ++u) issue_one(kt + 1, u, NS{});
         }
         __builtin_amdgcn_sched_barrier(0);
-      }
-      if (!M16 && ks == 0 && more && loader) {
-#pragma unroll
-        for (int u = LPT / 2; u < LPT; ++u) issue_one(kt + 1, u, NS{});
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -405,26 +272,20 @@ __global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kerne
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
   // Register r (0..15) of this lane's 32 x 32 block (i, j): its value and
-  // its row and column inside the block.  32 x 32 x 16 layout: column
-  // lane % 32, rows acc_row(r, lane / 32).  16 x 16 tiles (M16): tile
-  // (r / 8, r / 4 % 2) of the block, row 4 (lane / 16) + r % 4 of it,
-  // column lane % 16.  Registers 4q .. 4q+3 are four consecutive rows of
-  // one column in both layouts.
+  // its row and column inside the block: tile (r / 8, r / 4 % 2) of the block,
+  // row 4 (lane / 16) + r % 4 of it, column lane % 16.  Registers 4q .. 4q+3
+  // are four consecutive rows of one column.
   auto av = [&](int i, int j, int r) -> float {
-    if constexpr (M16) return acc[2 * i + (r >> 3)][2 * j + ((r >> 2) & 1)][r & 3];
-    else return acc[i][j][r];
+    return acc[2 * i + (r >> 3)][2 * j + ((r >> 2) & 1)][r & 3];
   };
-  auto arow = [&](int r) { return M16 ? 16 * (r >> 3) + 4 * (lane >> 4) + (r & 3) : acc_row(r, g); };
-  auto acol = [&](int r) { return M16 ? 16 * ((r >> 2) & 1) + (lane & 15) : col; };
-  // staging column flips: bit 5 every four rows (32 x 32: a lane group's
-  // rows are 8 apart) or bits 4..5 by row bits 2..3 (16 x 16: the four lane
-  // groups write rows 4 apart); both leave the row reads conflict-free
-  auto sidx = [](int r, int c) {
-    return M16 ? r * 64 + (c ^ (((r >> 2) & 3) << 4)) : r * 64 + (c ^ (((r >> 2) & 1) << 5));
-  };
-  // per-column bias and gate of the lane's columns: one per 32-column block,
-  // or two (the two 16-column tiles) in the M16 layout
-  constexpr int CS = M16 ? 2 : 1;
+  auto arow = [&](int r) { return 16 * (r >> 3) + 4 * (lane >> 4) + (r & 3); };
+  auto acol = [&](int r) { return 16 * ((r >> 2) & 1) + (lane & 15); };
+  // staging column flips: bits 4..5 by row bits 2..3 (the four lane groups
+  // write rows 4 apart), which leaves the row reads conflict-free
+  auto sidx = [](int r, int c) { return r * 64 + (c ^ (((r >> 2) & 3) << 4)); };
+  // per-column bias and gate of the lane's columns: two per 32-column block
+  // (its two 16-column tiles)
+  constexpr int CS = 2;
   float colv[TN][CS], gatev[TN][CS];
 #pragma unroll
   for (int j = 0; j < TN; ++j)
@@ -434,17 +295,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kerne
       colv[j][cs] = 0.f;
       gatev[j][cs] = 1.f;
       if (n < p.N) {
-        if constexpr (GA == GA_ROWS) {
-          const int r = p.rows[n];
-          if (bias_sg && r >= 0) colv[j][cs] = bias_sg[r];
-        } else {
-          if (bias_sg) colv[j][cs] = bias_sg[n];
-        }
+        if (bias_sg) colv[j][cs] = bias_sg[n];
         if (EPI == EPI_RESIDUAL && p.gate0) gatev[j][cs] = p.gate0[n] + (p.gate1 ? p.gate1[n] : 0.f);
       }
     }
-  // (register r's column set: r / 4 % 2 for M16)
-  auto csel = [](int r) { return M16 ? ((r >> 2) & 1) : 0; };
+  auto csel = [](int r) { return (r >> 2) & 1; };   // register r's column set
   constexpr int NPASS = (TM / 2) * (TN / 2);
   // A tile whose columns start at or past vt_col0 stores transposed (the
   // host keeps vt_col0 on a tile or segment boundary, so this is uniform).
@@ -594,30 +449,20 @@ __global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_nt_kerne
 // K-chunk table
 constexpr int kMaxKChunks = (160 * 1024 - 2 * 512 * G_BKC * 16) / 4;
 
-// 256 x 256 workgroup tile as 8 waves (2 x 4) of 128 x 64.
-constexpr int G_WGM = 2, G_WGN = 4, G_TM = 4, G_TN = 2;
-// Store-epilogue problems with fewer 256 x 256 tiles than half the CUs (the
-// 512 text tokens' K / V projection) take 128 x 128 tiles of 4 waves of
-// 64 x 64 instead, two workgroups per CU: four times the workgroups.
-constexpr int kSmallProblemTiles = 128;
-template <typename T, typename OutT, int EPI, int GA, int WGM, int WGN, int TM, int TN>
-void launch_cfg(const GemmParams<T, OutT>& p, hipStream_t stream) {
-  constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32;
-  const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN) * p.nseg;
-  const size_t dyn = GA == GA_KCH ? (size_t)(p.K / Chunk<T>::VEC) * sizeof(uint32_t) : 0;
-  hipLaunchKernelGGL((gemm_nt_kernel<T, OutT, EPI, GA, WGM, WGN, TM, TN, G_BKC>),
-                     dim3(tiles), dim3(64 * WGM * WGN), dyn, stream, p);
-}
+// The tile by pick_tile: 256 x 256 here (bf16 only, and not for row-gathered
+// B), any other shape in gemm_ring.h.
 template <typename T, typename OutT, int EPI, int GA>
-void launch_tile(const GemmParams<T, OutT>& p, hipStream_t stream) {
-  if constexpr (EPI == EPI_STORE) {
-    const int big = ((p.M + 255) / 256) * ((p.N + 255) / 256) * p.nseg;
-    if (big < kSmallProblemTiles) {
-      launch_cfg<T, OutT, EPI, GA, 2, 2, 2, 2>(p, stream);
-      return;
+hipError_t launch_tile(const GemmParams<T, OutT>& p, hipStream_t stream) {
+  const int shape = pick_tile<T>(p.M, p.N, p.nseg, p.K);
+  if constexpr (sizeof(T) == 2 && GA != GA_ROWS) {
+    if (shape == TS_256) {
+      const int tiles = ((p.M + 255) / 256) * ((p.N + 255) / 256) * p.nseg;
+      const size_t dyn = GA == GA_KCH ? (size_t)(p.K / Chunk<T>::VEC) * sizeof(uint32_t) : 0;
+      hipLaunchKernelGGL((gemm_nt_kernel<OutT, EPI, GA>), dim3(tiles), dim3(512), dyn, stream, p);
+      return hipGetLastError();
     }
   }
-  launch_cfg<T, OutT, EPI, GA, G_WGM, G_WGN, G_TM, G_TN>(p, stream);
+  return launch_gemm_ring<T, OutT>(shape, p, EPI, GA, stream);
 }
 
 template <typename T, typename OutT>
@@ -673,9 +518,9 @@ hipError_t launch_gemm(const T* A, int64_t lda, const T* B, int64_t ldb, OutT* C
   }
   if (!gather || (!gather->rows && !gather->kchunks)) {  // (segments allowed)
     switch (epi) {
-      case EPI_STORE: launch_tile<T, OutT, EPI_STORE, GA_NONE>(p, stream); break;
-      case EPI_GELU: launch_tile<T, OutT, EPI_GELU, GA_NONE>(p, stream); break;
-      default: launch_tile<T, OutT, EPI_RESIDUAL, GA_NONE>(p, stream); break;
+      case EPI_STORE: return launch_tile<T, OutT, EPI_STORE, GA_NONE>(p, stream);
+      case EPI_GELU: return launch_tile<T, OutT, EPI_GELU, GA_NONE>(p, stream);
+      default: return launch_tile<T, OutT, EPI_RESIDUAL, GA_NONE>(p, stream);
     }
   } else if (gather->rows && !gather->kchunks) {
     // the whole union matrix must stay addressable below the masked offset
@@ -684,8 +529,8 @@ hipError_t launch_gemm(const T* A, int64_t lda, const T* B, int64_t ldb, OutT* C
     p.rows = gather->rows;
     p.b_rows = gather->b_rows;
     switch (epi) {
-      case EPI_STORE: launch_tile<T, OutT, EPI_STORE, GA_ROWS>(p, stream); break;
-      case EPI_GELU: launch_tile<T, OutT, EPI_GELU, GA_ROWS>(p, stream); break;
+      case EPI_STORE: return launch_tile<T, OutT, EPI_STORE, GA_ROWS>(p, stream);
+      case EPI_GELU: return launch_tile<T, OutT, EPI_GELU, GA_ROWS>(p, stream);
       default: return hipErrorInvalidValue;
     }
   } else if (gather->kchunks && !gather->rows) {
@@ -693,11 +538,9 @@ hipError_t launch_gemm(const T* A, int64_t lda, const T* B, int64_t ldb, OutT* C
         (int64_t)BN_MAX * ldb * (int64_t)sizeof(T) >= (int64_t)kMasked)
       return hipErrorInvalidValue;
     p.kch = gather->kchunks;
-    launch_tile<T, OutT, EPI_RESIDUAL, GA_KCH>(p, stream);
-  } else {
-    return hipErrorInvalidValue;
+    if constexpr (std::is_same<T, OutT>::value) return launch_tile<T, OutT, EPI_RESIDUAL, GA_KCH>(p, stream);
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 // The chip's sustained MFMA rate with nothing else running: every CU holds
