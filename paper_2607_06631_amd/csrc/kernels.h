@@ -72,7 +72,8 @@ hipError_t launch_norm(const T* x, T* y, int M, int D, int mode, const float* p0
 
 // In place on rows of buf (stride ld): for each of nseg segments of width a
 // at column offset off[s]: y = x / sqrt(sum(x^2) * inv_norm_dim + eps) * gain[s][idx[c]]
-// (idx null: identity), times scale0 on segment 0,
+// (idx null: identity; else kept heads, whole runs of consecutive channels that
+// start at a multiple of the head width), times scale0 on segment 0,
 // then (rope != null) rotate consecutive pairs of each head_dim-wide head by
 // the token's 3D angles.
 struct RopeDesc {

@@ -4,7 +4,7 @@
 // kept in registers between the statistics and the apply pass, and written
 // once; statistics are fp32 whatever the storage type.
 #include <algorithm>
-
+#include <initializer_list>
 #include <type_traits>
 
 #include "common.h"
@@ -21,16 +21,68 @@ constexpr int R_ROWS = R_WAVES * R_RPW;
 // ---------------------------------------------------------------------------
 // LayerNorm (biased variance, eps) + AdaLN modulation or affine.
 // The workgroup first folds the per-column vectors into LDS (shift and
-// 1 + scale, or weight and bias); each wave then normalises R_RPW rows, one
-// row at a time: one statistics pass (sum and sum of squares of the row
-// shifted by its first element) with the row kept packed in registers, then
-// the apply pass.  Reductions are wave-local.
+// 1 + scale, or weight and bias) while its waves' first rows are on their way;
+// each wave then normalises its rows, one at a time: one statistics pass (sum
+// and sum of squares of the row shifted by its first element) with the row kept
+// packed in registers, then the apply pass.  Reductions are wave-local.
 // ---------------------------------------------------------------------------
-// The row kernels that stage per-column vectors in LDS run 16 waves per
-// workgroup, so the staging is shared by 128 rows (measured: 4.6 TB/s vs 3.3
-// TB/s with 4 waves on [32760, 5120] bf16).
+// The row kernels that stage per-column vectors in LDS run up to 16 waves of 8
+// rows per workgroup, so the staging is shared by 128 rows (measured: 4.6 TB/s
+// vs 3.3 TB/s with 4 waves on [32760, 5120] bf16).
 constexpr int NORM_WAVES = 16;
 constexpr int NORM_RPW = 8;
+
+// Rows per wave and waves per workgroup of the row kernels: about one workgroup
+// per CU, first by fewer rows per wave, then by fewer waves, never more than
+// the given maxima.  With 128 rows per workgroup whatever the row count, 1560
+// rows ran on 13 CUs and a wave's rows one after another: LayerNorm of
+// [1560, 5120] bf16 took 54 us (11 now), the q / k norm of 2 x [390, 4096]
+// 78 us (13).
+struct RowSplit {
+  int waves, rpw;
+};
+inline RowSplit row_split(int64_t rows, int max_waves, int max_rpw) {
+  constexpr int kWorkgroups = 256;
+  const int64_t per = (rows + kWorkgroups - 1) / kWorkgroups;   // rows per workgroup
+  if (per >= (int64_t)max_waves * max_rpw) return {max_waves, max_rpw};
+  if (per >= max_waves) return {max_waves, (int)((per + max_waves - 1) / max_waves)};
+  int w = 2;
+  while (w < per) w *= 2;
+  return {w < max_waves ? w : max_waves, 1};
+}
+
+// Staging of n per-column values (n a multiple of 4) by the whole workgroup,
+// four columns per thread and access: load(c) gives the values of columns
+// c .. c + 3, store(c, values) puts them in LDS.  A thread's U loads go out
+// together (columns past the end repeat the last four, so there is no branch
+// between them): with one turn at a time each was a memory round trip, ten in a
+// row for 5120 columns and two waves.
+template <int N>
+struct ColVecs {
+  f32x4 v[N];
+};
+template <int U, typename Load, typename Store>
+__device__ __forceinline__ void stage_columns(int n, Load&& load, Store&& store) {
+  const int stride = blockDim.x * 4;
+  for (int c0 = threadIdx.x * 4; c0 < n; c0 += U * stride) {
+    decltype(load(0)) v[U];
+    int c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      c[u] = min(c0 + u * stride, n - 4);
+      v[u] = load(c[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) store(c[u], v[u]);
+  }
+}
+
+// Whether every non-null pointer allows 16-byte accesses.
+inline bool aligned16(std::initializer_list<const void*> ps) {
+  uintptr_t u = 0;
+  for (const void* p : ps) u |= reinterpret_cast<uintptr_t>(p);
+  return u % 16 == 0;
+}
 
 // 16-byte chunks each lane holds for a row of D elements, rounded up to one
 // of the instantiated register budgets (4, 8, 12, 16); 0 if D is too wide.
@@ -39,42 +91,71 @@ inline int chunks_per_lane(int D) {
   const int c = (D / Chunk<T>::VEC + kWave - 1) / kWave;
   return c <= 4 ? 4 : c <= 8 ? 8 : c <= 12 ? 12 : c <= R_MAXC ? R_MAXC : 0;
 }
+// vec: every per-column vector is there and allows 16-byte loads (D is a
+// multiple of 64).
 template <typename T, int MAXC>
 __global__ __launch_bounds__(64 * NORM_WAVES) void norm_kernel(const T* __restrict__ x, T* __restrict__ y,
                                                          int M, int D, int mode, const float* p0,
                                                          const float* p1, const float* p2,
-                                                         const float* p3, float eps) {
+                                                         const float* p3, float eps, int rpw, int vec) {
   constexpr int VEC = Chunk<T>::VEC;
   extern __shared__ float vec_lds[];  // [2][D]: multiplier, addend
   float* mul = vec_lds;
   float* add = vec_lds + D;
-  for (int n = threadIdx.x; n < D; n += 64 * NORM_WAVES) {
-    if (mode == 0) {
-      mul[n] = 1.f + p2[n] + (p3 ? p3[n] : 0.f);
-      add[n] = p0[n] + (p1 ? p1[n] : 0.f);
-    } else {
-      mul[n] = p0[n];
-      add[n] = p1[n];
+  const int lane = threadIdx.x & 63;
+  const int nch = D / VEC;
+  const int nwaves = blockDim.x >> 6;
+  const int64_t row0 = ((int64_t)blockIdx.x * nwaves + (threadIdx.x >> 6)) * rpw;
+  u32x4 raw[MAXC];
+  auto load_row = [&](int64_t row) {
+    const T* xr = x + row * D;
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {
+      const int c = lane + kWave * i;
+      if (c < nch) raw[i] = *reinterpret_cast<const u32x4*>(xr + c * VEC);
+    }
+  };
+  // (16 chunks per lane leave no registers to hold a row meanwhile)
+  constexpr bool AHEAD = MAXC <= 12;
+  if (AHEAD && row0 < M) load_row(row0);
+  auto ld4 = [](const float* p) { return *reinterpret_cast<const f32x4*>(p); };
+  if (vec && mode == 0) {
+    stage_columns<4>(D, [&](int n) { return ColVecs<4>{ld4(p0 + n), ld4(p1 + n), ld4(p2 + n), ld4(p3 + n)}; },
+                     [&](int n, const ColVecs<4>& v) {
+                       *reinterpret_cast<f32x4*>(mul + n) = 1.f + v.v[2] + v.v[3];
+                       *reinterpret_cast<f32x4*>(add + n) = v.v[0] + v.v[1];
+                     });
+  } else if (vec) {
+    stage_columns<4>(D, [&](int n) { return ColVecs<2>{ld4(p0 + n), ld4(p1 + n)}; },
+                     [&](int n, const ColVecs<2>& v) {
+                       *reinterpret_cast<f32x4*>(mul + n) = v.v[0];
+                       *reinterpret_cast<f32x4*>(add + n) = v.v[1];
+                     });
+  } else {
+    for (int n = threadIdx.x; n < D; n += blockDim.x) {
+      if (mode == 0) {
+        mul[n] = 1.f + p2[n] + (p3 ? p3[n] : 0.f);
+        add[n] = p0[n] + (p1 ? p1[n] : 0.f);
+      } else {
+        mul[n] = p0[n];
+        add[n] = p1[n];
+      }
     }
   }
   __syncthreads();
-  const int lane = threadIdx.x & 63;
-  const int nch = D / VEC;
   const float inv_d = 1.f / (float)D;
-  for (int rr = 0; rr < NORM_RPW; ++rr) {
-    const int64_t row = (int64_t)blockIdx.x * (NORM_WAVES * NORM_RPW) + (threadIdx.x >> 6) * NORM_RPW + rr;
+  for (int rr = 0; rr < rpw; ++rr) {
+    const int64_t row = row0 + rr;
     if (row >= M) break;
-    const T* xr = x + row * D;
-    u32x4 raw[MAXC];
+    if (!AHEAD || rr > 0) load_row(row);
     // one pass over shifted data: sum and sum of squares of (x - x0), where
     // x0 is the row's first element, keep the variance free of cancellation
-    const float x0 = to_f32(xr[0]);
+    const float x0 = to_f32(x[row * D]);
     float s = 0.f, ss = 0.f;
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
       const int c = lane + kWave * i;
       if (c < nch) {
-        raw[i] = *reinterpret_cast<const u32x4*>(xr + c * VEC);
         float v[VEC];
         Chunk<T>::unpack(raw[i], v);
 #pragma unroll
@@ -115,17 +196,20 @@ template <typename T>
 hipError_t launch_norm(const T* x, T* y, int M, int D, int mode, const float* p0, const float* p1,
                        const float* p2, const float* p3, float eps, hipStream_t stream) {
   if (M <= 0) return hipSuccess;
-  const dim3 grid((M + NORM_WAVES * NORM_RPW - 1) / (NORM_WAVES * NORM_RPW));
+  const RowSplit rs = row_split(M, NORM_WAVES, NORM_RPW);
+  const int rows_per_wg = rs.waves * rs.rpw;
+  const dim3 grid((M + rows_per_wg - 1) / rows_per_wg), block(64 * rs.waves);
   const size_t lds = 2 * D * sizeof(float);
+  const int vec = p0 && p1 && (mode != 0 || (p2 && p3)) && aligned16({p0, p1, p2, p3});
+  auto launch = [&](auto c_tag) {
+    hipLaunchKernelGGL((norm_kernel<T, decltype(c_tag)::value>), grid, block, lds, stream, x, y, M, D,
+                       mode, p0, p1, p2, p3, eps, rs.rpw, vec);
+  };
   switch (chunks_per_lane<T>(D)) {
-    case 4: hipLaunchKernelGGL((norm_kernel<T, 4>), grid, dim3(64 * NORM_WAVES), lds, stream, x, y, M,
-                               D, mode, p0, p1, p2, p3, eps); break;
-    case 8: hipLaunchKernelGGL((norm_kernel<T, 8>), grid, dim3(64 * NORM_WAVES), lds, stream, x, y, M,
-                               D, mode, p0, p1, p2, p3, eps); break;
-    case 12: hipLaunchKernelGGL((norm_kernel<T, 12>), grid, dim3(64 * NORM_WAVES), lds, stream, x, y,
-                                M, D, mode, p0, p1, p2, p3, eps); break;
-    case 16: hipLaunchKernelGGL((norm_kernel<T, 16>), grid, dim3(64 * NORM_WAVES), lds, stream, x, y,
-                                M, D, mode, p0, p1, p2, p3, eps); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 8: launch(std::integral_constant<int, 8>{}); break;
+    case 12: launch(std::integral_constant<int, 12>{}); break;
+    case 16: launch(std::integral_constant<int, 16>{}); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -141,45 +225,76 @@ hipError_t launch_norm(const T* x, T* y, int M, int D, int mode, const float* p0
 // them, with the rotation-table reads in their shadow.
 // ---------------------------------------------------------------------------
 constexpr int QK_WAVES = 8;    // 16 KB of loads in flight per wave; registers for both segments
-// Rows per wave.  One segment: 4, so 32760 video tokens make 1024 workgroups,
-// several per CU, with more rows' loads in flight (5.3 TB/s; 16 rows per
-// wave, one workgroup per CU, reached 4.2).  Two segments (q and k, twice the
-// loads per row): 16 (5.4-5.5 TB/s against 5.3 with 4).
+// Rows per wave where there are rows enough for a workgroup per CU.  One
+// segment: 4, so 32760 video tokens make 1024 workgroups, several per CU, with
+// more rows' loads in flight (5.3 TB/s; 16 rows per wave, one workgroup per CU,
+// reached 4.2).  Two segments (q and k, twice the loads per row): 16 (5.4-5.5
+// TB/s against 5.3 with 4).  Below that 4 (two segments), then 1, the latter
+// with fewer waves per workgroup (row_split).
 template <int NSEG>
 constexpr int qk_rpw() { return NSEG == 2 ? 16 : 4; }
-template <typename T, int MAXC, int NSEG>
+template <typename T, int MAXC, int NSEG, int RPW>
 __global__ __launch_bounds__(64 * QK_WAVES) void qk_norm_kernel(T* buf, int64_t ld, int rows, int a,
                                                             int nseg, int off0, int off1,
                                                             const float* g0, const float* g1,
                                                             const int32_t* gidx, float scale0,
-                                                            float inv_dim, float eps, RopeDesc rope) {
+                                                            float inv_dim, float eps, RopeDesc rope,
+                                                            int vec) {
   constexpr int VEC = Chunk<T>::VEC;
   constexpr int NP = VEC / 2;  // pairs per chunk
   extern __shared__ float gain_lds[];  // [nseg][a]
-  for (int n = threadIdx.x; n < a; n += 64 * QK_WAVES) {
-    const int gn = gidx ? gidx[n] : n;
-    gain_lds[n] = g0[gn] * scale0;
-    if (nseg > 1) gain_lds[a + n] = g1[gn];
-  }
-  __syncthreads();
   const int lane = threadIdx.x & 63;
   const int nch = a / VEC;
   const int jb = ((lane * VEC) % rope.head_dim) / 2;  // first head-local pair of this lane
-  constexpr int RPW = qk_rpw<NSEG>();
-  for (int rr = 0; rr < RPW; ++rr) {
-    const int64_t row = (int64_t)blockIdx.x * (QK_WAVES * RPW) + (threadIdx.x >> 6) * RPW + rr;
-    if (row >= rows) break;
-    // both segments' loads go out before anything waits on them
-    u32x4 raw[NSEG][MAXC];
+  const int nwaves = blockDim.x >> 6;
+  const int64_t row0 = ((int64_t)blockIdx.x * nwaves + (threadIdx.x >> 6)) * RPW;
+  auto load_row = [&](int64_t row, u32x4 (&dst)[NSEG][MAXC]) {   // both segments' loads together
 #pragma unroll
     for (int sg = 0; sg < NSEG; ++sg) {
       const T* xr = buf + row * ld + (sg == 0 ? off0 : off1);
 #pragma unroll
       for (int i = 0; i < MAXC; ++i) {
         const int c = lane + kWave * i;
-        if (c < nch) raw[sg][i] = *reinterpret_cast<const u32x4*>(xr + c * VEC);
+        if (c < nch) dst[sg][i] = *reinterpret_cast<const u32x4*>(xr + c * VEC);
       }
     }
+  };
+  // a lone row is on its way during the staging; of several, the compiler
+  // overlaps one's loads with the others' work (RPW is a constant for that:
+  // with a run-time count the wide two-segment launch took 312 us, not 170)
+  u32x4 lone[NSEG][MAXC];
+  if constexpr (RPW == 1) {
+    if (row0 < rows) load_row(row0, lone);
+  }
+  auto ld4 = [](const float* p) { return *reinterpret_cast<const f32x4*>(p); };
+  if (vec) {   // 16-byte gain loads (a is whole heads, and so are the runs of a gain table)
+    stage_columns<4>(
+        a,
+        [&](int n) {
+          const int gn = gidx ? gidx[n] : n;
+          ColVecs<NSEG> v;
+          v.v[0] = ld4(g0 + gn) * scale0;
+          if constexpr (NSEG > 1) v.v[1] = ld4(g1 + gn);
+          return v;
+        },
+        [&](int n, const ColVecs<NSEG>& v) {
+          *reinterpret_cast<f32x4*>(gain_lds + n) = v.v[0];
+          if constexpr (NSEG > 1) *reinterpret_cast<f32x4*>(gain_lds + a + n) = v.v[1];
+        });
+  } else {
+    for (int n = threadIdx.x; n < a; n += blockDim.x) {
+      const int gn = gidx ? gidx[n] : n;
+      gain_lds[n] = g0[gn] * scale0;
+      if (nseg > 1) gain_lds[a + n] = g1[gn];
+    }
+  }
+  __syncthreads();
+  for (int rr = 0; rr < RPW; ++rr) {
+    const int64_t row = row0 + rr;
+    if (row >= rows) break;
+    u32x4 own[NSEG][MAXC];
+    if constexpr (RPW > 1) load_row(row, own);
+    u32x4(&raw)[NSEG][MAXC] = RPW > 1 ? own : lone;
     // rotation factors of this lane's pairs (table reads overlap the loads)
     float cs[NP], sn[NP];
     if (rope.table) {
@@ -259,16 +374,24 @@ hipError_t launch_qk_norm(T* buf, int64_t ld, int rows, int a, int nseg, int off
   if (rd.head_dim <= 0) rd.head_dim = 64;   // no rotation: any width dividing 64 * VEC
   constexpr int VEC = Chunk<T>::VEC;
   if ((64 * VEC) % rd.head_dim != 0) return hipErrorInvalidValue;
+  const int vec = aligned16({g0, g1});
   // q and k in one launch while both fit the registers (up to 8 chunks per
   // lane), else one launch per segment
   auto launch = [&](auto c_tag, auto nseg_tag, int off_a, int off_b, const float* ga,
                     const float* gb, float sa) {
     constexpr int C = decltype(c_tag)::value, NS = decltype(nseg_tag)::value;
-    constexpr int rows_per_wg = QK_WAVES * qk_rpw<NS>();
-    const dim3 grid((rows + rows_per_wg - 1) / rows_per_wg);
-    hipLaunchKernelGGL((qk_norm_kernel<T, C, NS>), grid, dim3(64 * QK_WAVES), NS * a * sizeof(float),
-                       stream, buf, ld, rows, a, NS, off_a, off_b, ga, gb, gain_idx, sa,
-                       inv_norm_dim, eps, rd);
+    const RowSplit rs = row_split(rows, QK_WAVES, qk_rpw<NS>());
+    auto go = [&](auto rpw_tag) {
+      constexpr int RPW = decltype(rpw_tag)::value;
+      const int rows_per_wg = rs.waves * RPW;
+      const dim3 grid((rows + rows_per_wg - 1) / rows_per_wg);
+      hipLaunchKernelGGL((qk_norm_kernel<T, C, NS, RPW>), grid, dim3(64 * rs.waves),
+                         NS * a * sizeof(float), stream, buf, ld, rows, a, NS, off_a, off_b, ga, gb,
+                         gain_idx, sa, inv_norm_dim, eps, rd, vec);
+    };
+    if (rs.rpw == qk_rpw<NS>()) go(std::integral_constant<int, qk_rpw<NS>()>{});
+    else if (NS == 2 && rs.rpw >= 4) go(std::integral_constant<int, 4>{});
+    else go(std::integral_constant<int, 1>{});
   };
   auto by_chunks = [&](auto c_tag) {
     constexpr int C = decltype(c_tag)::value;
