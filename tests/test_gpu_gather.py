@@ -1,0 +1,51 @@
+"""The plan's gather of kept rows and columns, checked exactly on the reordered
+FFN weights (the same launches: rows of W1 and b1, columns of W2 by an arbitrary
+permutation) at widths that take each path: whole 16-byte vectors, a width that
+is none, source or destination addresses off a 16-byte boundary, row counts that
+are not a multiple of a lane's rows.  Kept runs and dropped entries are covered
+bit for bit by the compact / indexed plan tests.
+"""
+import numpy as np
+import pytest
+
+from paper_2607_06631_amd import binding as B
+from tests.gpu_util import say
+from workloads import get_config, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _at(t, shift):
+    """A copy of t that starts `shift` elements past a 256-byte boundary."""
+    import torch
+    buf = torch.empty(t.numel() + 64, dtype=t.dtype, device="cuda")
+    v = buf[shift:shift + t.numel()].view(t.shape)
+    v.copy_(t)
+    return v
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("ffn", [1, 64, 203, 1030])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_reordered_weights_are_the_permuted_ones(dtype, ffn, shift):
+    import ctypes as C
+    import torch
+    cfg = get_config("tiny").with_(ffn_dim=ffn, n_layers=1, dtype=dtype, ffn_chunk=1,
+                                   head_dim=64 if dtype == "f32" else 128, n_heads=4 if dtype == "f32" else 2)
+    say(f"gather {dtype} ffn={ffn} shift={shift}")
+    w = B.upload_weights(synth.make_weights(cfg, seed=3), dtype)
+    lw = w["layers"][0]
+    for k in ("ffn_w1", "ffn_w2", "ffn_b1"):
+        lw[k] = _at(lw[k], shift)
+    model = B.dif_model_create(cfg, w)
+    w1, w2, b1 = (_at(torch.zeros_like(lw[k]), shift) for k in ("ffn_w1", "ffn_w2", "ffn_b1"))
+    scratch = torch.empty(ffn * 12 + 16, dtype=torch.uint8, device="cuda")
+    perm = np.zeros(ffn, np.int32)
+    B._check(B.lib().dif_ffn_reorder(model.handle, 0, w1.data_ptr(), b1.data_ptr(), w2.data_ptr(),
+                                     perm.ctypes.data, scratch.data_ptr(), scratch.numel(), None))
+    torch.cuda.synchronize()
+    p = torch.from_numpy(perm.astype(np.int64)).cuda()
+    assert sorted(perm.tolist()) == list(range(ffn))
+    assert torch.equal(w1, lw["ffn_w1"][p])
+    assert torch.equal(w2, lw["ffn_w2"][:, p])
+    assert torch.equal(b1, lw["ffn_b1"][p])
