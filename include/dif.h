@@ -253,7 +253,7 @@ dif_status dif_step_forward(const dif_plan* plan, const float* z, float t, const
  *
  * dif_text_cache_bytes: device bytes of the cache for B samples of Lc text
  * tokens (per layer B*Lc*D keys and B*D*round_up(Lc, 64) transposed values
- * in the model dtype, plus one B*Lc*D staging buffer).
+ * in the model dtype, plus one B*Lc*D buffer that is not written).
  * dif_text_cache_build: fills `cache` (caller-owned device memory, 256-byte
  * aligned, cache_bytes >= the size above) from ctx [B, Lc, D] (dtype),
  * enqueued on `stream`; 4*B*Lc*D*D*n_layers flops.  The cache stays valid

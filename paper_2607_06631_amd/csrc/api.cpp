@@ -405,8 +405,8 @@ WsLayout ws_layout(const dif_config& c, int B, int L, int Lc) {
 
 // Cross-attention text cache: per layer, the text tokens' keys before their
 // RMSNorm, k = ctx W_ck^T + b_ck [B*Lc, D], and values transposed,
-// v^T [B, D, ldcvt] (zero past Lc), for all heads; then one [B*Lc, D]
-// staging buffer used while building.
+// v^T [B, D, ldcvt] (zero past Lc), for all heads; then one [B*Lc, D] buffer
+// that the size has always had (nothing is staged there any more).
 struct TextLayout {
   size_t k_bytes, vt_bytes, per_layer, stage, total;
   int64_t ldcvt;
@@ -573,13 +573,12 @@ dif_status block_impl(const dif_plan* plan, int layer, T* x, const T* ctx, const
   if (a > 0) {
     // q and k go to `big` (row-major, for QK-norm in place); v is written
     // transposed into vt [B, a, ldvt] by the same launch, as attention reads
-    // it, when the v columns start on a GEMM tile (always for head width 128
-    // and for indexed plans, where v is a launch segment of its own); else v
-    // is stored with q and k and transposed by its own kernel
-    const bool vt_in_gemm = ix || (2 * a) % 256 == 0;
+    // it.  The v columns start on a GEMM tile: in one B matrix when they are a
+    // multiple of 256 (any even count of 128-wide heads), else as a launch
+    // segment of their own, like q and k.
     const dif::GemmVt vtd{vt, wl.ldvt, 2 * a, a, L};
+    dif::GemmGather g = g_self_rows;
     if (ix) {
-      dif::GemmGather g = g_self_rows;
       g.nseg = 3;
       g.seg_b[0] = W.self_wk;
       g.seg_b[1] = W.self_wv;
@@ -588,9 +587,19 @@ dif_status block_impl(const dif_plan* plan, int layer, T* x, const T* ctx, const
       DIF_TRY((gemm<T, T>(PK_GEMM_QKV, xn, D, (const T*)W.self_wq, D, big, 3 * a, M, a, D,
                           dif::EPI_STORE, W.self_bq, nullptr, nullptr, s, &g, &vtd)));
     } else {
-      DIF_TRY((gemm<T, T>(PK_GEMM_QKV, xn, D, lp.at<T>(lp.o_wqkv), D, big, 3 * a, M, 3 * a, D,
-                          dif::EPI_STORE, lp.at<float>(lp.o_bqkv), nullptr, nullptr, s, nullptr,
-                          vt_in_gemm ? &vtd : nullptr)));
+      const T* w = lp.at<T>(lp.o_wqkv);
+      const float* bias = lp.at<float>(lp.o_bqkv);
+      const bool one = (2 * a) % 256 == 0;
+      g = dif::GemmGather{};
+      if (!one) {
+        g.nseg = 3;
+        for (int i = 1; i < 3; ++i) {
+          g.seg_b[i - 1] = w + (size_t)i * a * D;
+          g.seg_bias[i - 1] = bias + (size_t)i * a;
+        }
+      }
+      DIF_TRY((gemm<T, T>(PK_GEMM_QKV, xn, D, w, D, big, 3 * a, M, one ? 3 * a : a, D, dif::EPI_STORE,
+                          bias, nullptr, nullptr, s, &g, &vtd)));
     }
     {
       ProfScope ps(PK_QK_NORM, s, 0, 4.0 * M * a * es);
@@ -599,10 +608,6 @@ dif_status block_impl(const dif_plan* plan, int layer, T* x, const T* ctx, const
       HIP_TRY(dif::launch_qk_norm<T>(big, 3 * a, M, a, 2, 0, a, ix ? W.self_gq : lp.at<float>(lp.o_gq),
                                      ix ? W.self_gk : lp.at<float>(lp.o_gk), inv_d, c.eps, &rd, s,
                                      ix ? rs : nullptr, q_scale));
-    }
-    if (!vt_in_gemm) {
-      ProfScope ps(PK_TRANSPOSE, s, 0, 2.0 * M * a * es);
-      HIP_TRY(dif::launch_transpose_vt<T>(big + 2 * a, 3 * a, a, B, L, vt, wl.ldvt, s));
     }
     DIF_TRY(attention<T>(PK_ATTN_SELF, dh, big, 3 * a, big + a, 3 * a, vt, wl.ldvt, o, a, B, L, L,
                          lp.info.self_heads, s, true,
@@ -626,42 +631,46 @@ dif_status block_impl(const dif_plan* plan, int layer, T* x, const T* ctx, const
     // all-head projections (the same values the projection below computes:
     // each output element's reduction is independent of which rows are kept).
     const bool cached = tk != nullptr;
-    const int ldk = cached ? ac : 2 * ac;
     if (ix)
       DIF_TRY((gemm<T, T>(PK_GEMM_CROSS_Q, xn, D, (const T*)W.cross_wq, D, cq, ac, M, ac, D,
                           dif::EPI_STORE, W.cross_bq, nullptr, nullptr, s, &g_cross_rows)));
     else
       DIF_TRY((gemm<T, T>(PK_GEMM_CROSS_Q, xn, D, lp.at<T>(lp.o_wcq), D, cq, ac, M, ac, D,
                           dif::EPI_STORE, lp.at<float>(lp.o_bcq), nullptr, nullptr, s)));
+    // the text keys before their norm, and V^T: two segments of one launch
+    // (V^T by its epilogue), or the cache's kept heads (the norm below reads
+    // the keys through the head table)
     if (cached) {
-      ProfScope ps(PK_GATHER, s, 0, 4.0 * Mc * ac * es);
-      HIP_TRY(dif::launch_gather_cols16<T>(tk, D, ckv, ldk, Mc, ac, rc, s));
+      ProfScope ps(PK_GATHER, s, 0, 2.0 * Mc * ac * es);
       HIP_TRY(dif::launch_gather_rows16<T>(tvt, (int64_t)D * wl.ldcvt, cvt, (int64_t)ac * wl.ldcvt,
                                            wl.ldcvt, ac, B, rc, s));
-    } else if (ix) {
-      dif::GemmGather g = g_cross_rows;
-      g.nseg = 2;
-      g.seg_b[0] = W.cross_wv;
-      g.seg_bias[0] = W.cross_bv;
-      DIF_TRY((gemm<T, T>(PK_GEMM_CROSS_KV, ctx, D, (const T*)W.cross_wk, D, ckv, 2 * ac, Mc, ac, D,
-                          dif::EPI_STORE, W.cross_bk, nullptr, nullptr, s, &g)));
     } else {
-      DIF_TRY((gemm<T, T>(PK_GEMM_CROSS_KV, ctx, D, lp.at<T>(lp.o_wckv), D, ckv, 2 * ac, Mc, 2 * ac, D,
-                          dif::EPI_STORE, lp.at<float>(lp.o_bckv), nullptr, nullptr, s)));
+      const dif::GemmVt vtd{cvt, wl.ldcvt, ac, ac, Lc};
+      dif::GemmGather g;
+      if (ix) g = g_cross_rows;
+      const T* wk = ix ? (const T*)W.cross_wk : lp.at<T>(lp.o_wckv);
+      const float* bk = ix ? W.cross_bk : lp.at<float>(lp.o_bckv);
+      g.nseg = 2;
+      g.seg_b[0] = ix ? (const T*)W.cross_wv : wk + (size_t)ac * D;
+      g.seg_bias[0] = ix ? W.cross_bv : bk + ac;
+      DIF_TRY((gemm<T, T>(PK_GEMM_CROSS_KV, ctx, D, wk, D, ckv, ac, Mc, ac, D, dif::EPI_STORE, bk,
+                          nullptr, nullptr, s, &g, &vtd)));
     }
     {
       ProfScope ps(PK_QK_NORM, s, 0, 2.0 * (M + Mc) * ac * es);
+      // one launch for the video queries and the text keys
+      dif::RopeDesc rd{};
+      rd.rows1 = Mc;
+      rd.src1 = cached ? tk : ckv;
+      rd.lds1 = cached ? D : ac;
+      rd.src_idx1 = cached ? rc : nullptr;
+      rd.dst1 = ckv;
+      rd.ldd1 = ac;
+      rd.gain1 = ix ? W.cross_gk : lp.at<float>(lp.o_gck);
       HIP_TRY(dif::launch_qk_norm<T>(cq, ac, M, ac, 1, 0, 0, ix ? W.cross_gq : lp.at<float>(lp.o_gcq),
-                                     nullptr, inv_d, c.eps, nullptr, s, ix ? rc : nullptr, q_scale));
-      HIP_TRY(dif::launch_qk_norm<T>(ckv, ldk, Mc, ac, 1, 0, 0,
-                                     ix ? W.cross_gk : lp.at<float>(lp.o_gck), nullptr, inv_d, c.eps,
-                                     nullptr, s, ix ? rc : nullptr));
+                                     nullptr, inv_d, c.eps, &rd, s, ix ? rc : nullptr, q_scale));
     }
-    if (!cached) {
-      ProfScope ps(PK_TRANSPOSE, s, 0, 2.0 * Mc * ac * es);
-      HIP_TRY(dif::launch_transpose_vt<T>(ckv + ac, 2 * ac, ac, B, Lc, cvt, wl.ldcvt, s));
-    }
-    DIF_TRY(attention<T>(PK_ATTN_CROSS, dh, cq, ac, ckv, ldk, cvt, wl.ldcvt, o, ac, B, L, Lc,
+    DIF_TRY(attention<T>(PK_ATTN_CROSS, dh, cq, ac, ckv, ac, cvt, wl.ldcvt, o, ac, B, L, Lc,
                          lp.info.cross_heads, s, true));
   }
   if (ix)
@@ -718,17 +727,19 @@ dif_status text_cache_impl(const dif_model* m, const T* ctx, int B, int Lc, char
                            const TextLayout& tl, hipStream_t s) {
   const dif_config& c = m->cfg;
   const int D = c.dim, Mc = B * Lc;
-  T* stage = reinterpret_cast<T*>(cache + tl.stage);
   for (int l = 0; l < c.n_layers; ++l) {
     const dif_layer_weights& W = m->layers[l];
     T* k = reinterpret_cast<T*>(cache + tl.k(l));
-    T* vt = reinterpret_cast<T*>(cache + tl.vt(l));
+    // keys and values as two segments of one launch, the values transposed by
+    // its epilogue (as two launches and a transpose: 81 us a layer for 512
+    // tokens at D = 5120, each launch 160-240 tiles)
+    const dif::GemmVt vtd{cache + tl.vt(l), tl.ldcvt, D, D, Lc, true};
+    dif::GemmGather g;
+    g.nseg = 2;
+    g.seg_b[0] = W.cross_wv;
+    g.seg_bias[0] = W.cross_bv;
     DIF_TRY((gemm<T, T>(PK_GEMM_CROSS_KV, ctx, D, (const T*)W.cross_wk, D, k, D, Mc, D, D,
-                        dif::EPI_STORE, W.cross_bk, nullptr, nullptr, s)));
-    DIF_TRY((gemm<T, T>(PK_GEMM_CROSS_KV, ctx, D, (const T*)W.cross_wv, D, stage, D, Mc, D, D,
-                        dif::EPI_STORE, W.cross_bv, nullptr, nullptr, s)));
-    ProfScope ps(PK_TRANSPOSE, s, 0, 2.0 * Mc * D * sizeof(T));
-    HIP_TRY(dif::launch_transpose_vt<T>(stage, D, D, B, Lc, vt, tl.ldcvt, s));
+                        dif::EPI_STORE, W.cross_bk, nullptr, nullptr, s, &g, &vtd)));
   }
   return DIF_OK;
 }

@@ -65,6 +65,7 @@ struct GemmParams {
   int64_t ldvt;
   int vt_col0, vt_dims, vt_L;
   int vt_vec4;           // vt rows allow aligned 4-element stores and vt_L % 4 == 0
+  int vt_pad;            // columns vt_L .. ldvt are zeroed
 };
 
 // four consecutive output elements: 8-byte (bf16) or 16-byte (f32) accesses
@@ -79,6 +80,32 @@ __device__ __forceinline__ void store4(float* p, const float* v) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) x[e] = v[e];
   *reinterpret_cast<f32x4*>(p) = x;
+}
+
+// Four consecutive rows m .. m+3 (m a multiple of 4, m < M) of transposed
+// column `dim`.  The lane that stores a sample's last token zeroes the padding.
+template <typename T, typename OutT>
+__device__ __forceinline__ void store_vt4(const GemmParams<T, OutT>& p, int m, int dim, const float* v) {
+  auto pad = [&](OutT* row) {
+    if (p.vt_pad)
+      for (int64_t j = p.vt_L; j < p.ldvt; ++j) row[j] = from_f32<OutT>(0.f);
+  };
+  const int bb = m / p.vt_L, jt = m - bb * p.vt_L;
+  if (p.vt_vec4 && m + 4 <= p.M) {   // same sample, aligned
+    OutT* row = p.vt + ((int64_t)bb * p.vt_dims + dim) * p.ldvt;
+    store4(row + jt, v);
+    if (jt + 4 == p.vt_L) pad(row);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int me = m + e;
+      if (me >= p.M) break;
+      const int be = me / p.vt_L, je = me - be * p.vt_L;
+      OutT* row = p.vt + ((int64_t)be * p.vt_dims + dim) * p.ldvt;
+      row[je] = from_f32<OutT>(v[e]);
+      if (je + 1 == p.vt_L) pad(row);
+    }
+  }
 }
 
 // Logical tile of this workgroup: XCD-contiguous ranges of tiles, then groups

@@ -331,27 +331,14 @@ __global__ __launch_bounds__(512, 1) void gemm_nt_kernel(GemmParams<bf16, OutT> 
         wave_sync();
         const int q4 = lane & 15;                                    // 4-token group
         const int m = m0 + wm * TM * 32 + rb * 64 + 4 * q4;          // its first token
-        const int bb = m / p.vt_L, jt = m - bb * p.vt_L;
-        const bool full4 = p.vt_vec4 && m + 4 <= p.M;                // same sample, aligned
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
           const int dl = t * 4 + (lane >> 4);                        // dim within the pass
           const int n = n0 + wn * TN * 32 + ch * 64 + dl;
           const f32x4 sv = *reinterpret_cast<const f32x4*>(&stage[tidx(dl, 4 * q4)]);
           if (n >= p.N || m >= p.M) continue;
-          const int dim = sg * p.N + n - p.vt_col0;
-          float v[4] = {sv[0], sv[1], sv[2], sv[3]};
-          if (full4) {
-            store4(p.vt + ((int64_t)bb * p.vt_dims + dim) * p.ldvt + jt, v);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int me = m + e;
-              if (me >= p.M) break;
-              const int be = me / p.vt_L, je = me - be * p.vt_L;
-              p.vt[((int64_t)be * p.vt_dims + dim) * p.ldvt + je] = from_f32<OutT>(v[e]);
-            }
-          }
+          const float v[4] = {sv[0], sv[1], sv[2], sv[3]};
+          store_vt4(p, m, sg * p.N + n - p.vt_col0, v);
         }
         if (ps + 1 < NPASS) wave_sync();
       }
@@ -505,6 +492,7 @@ hipError_t launch_gemm(const T* A, int64_t lda, const T* B, int64_t ldb, OutT* C
     p.vt_col0 = vt->col0;
     p.vt_dims = vt->dims;
     p.vt_L = vt->L;
+    p.vt_pad = vt->zero_pad;
     p.vt_vec4 = vt->L % 4 == 0 && vt->ldvt % 4 == 0 &&
                 reinterpret_cast<uintptr_t>(vt->vt) % (4 * sizeof(OutT)) == 0;
   }

@@ -342,27 +342,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_ring_kernel(GemmPara
 #pragma unroll
       for (int i = 0; i < AM; ++i) {
         const int m = mw + i * 16 + 4 * g;
-        const int bb = m / p.vt_L, jt = m - bb * p.vt_L;
-        const bool full4 = p.vt_vec4 && m + 4 <= p.M;
 #pragma unroll
         for (int j = 0; j < AN; ++j) {
           const int n = nw + j * 16 + col;
           if (n >= p.N || m >= p.M) continue;
-          const int dim = sg * p.N + n - p.vt_col0;
           float v[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e] + colv[j];
-          if (full4) {
-            store4(p.vt + ((int64_t)bb * p.vt_dims + dim) * p.ldvt + jt, v);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int me = m + e;
-              if (me >= p.M) break;
-              const int be = me / p.vt_L, je = me - be * p.vt_L;
-              p.vt[((int64_t)be * p.vt_dims + dim) * p.ldvt + je] = from_f32<OutT>(v[e]);
-            }
-          }
+          store_vt4(p, m, sg * p.N + n - p.vt_col0, v);
         }
       }
       return;

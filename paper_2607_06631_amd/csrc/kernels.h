@@ -20,9 +20,9 @@ enum Epi { EPI_STORE = 0, EPI_GELU = 1, EPI_RESIDUAL = 2 };
 //            segments share A and the row table, segment s writes C columns
 //            [s*N, (s+1)*N).  Epilogues STORE and GELU.
 struct GemmGather {
-  const int32_t* rows;
-  const int32_t* kchunks;
-  int b_rows;
+  const int32_t* rows = nullptr;
+  const int32_t* kchunks = nullptr;
+  int b_rows = 0;
   int nseg = 1;
   const void* seg_b[2] = {nullptr, nullptr};
   const float* seg_bias[2] = {nullptr, nullptr};
@@ -31,12 +31,14 @@ struct GemmGather {
 // Transposed output for the columns of a store-epilogue GEMM from output
 // column col0 on (col0 on a 256-column tile boundary, or the first column of
 // a segment): column col0 + d of row m = b * L + j goes to
-// vt[(b * dims + d) * ldvt + j].  Used to write V^T straight from the QKV
-// projection.
+// vt[(b * dims + d) * ldvt + j].  Used to write V^T straight from the QKV and
+// text K / V projections.  zero_pad: columns L .. ldvt of every V^T row are
+// written as zeros.
 struct GemmVt {
   void* vt;
   int64_t ldvt;
   int col0, dims, L;
+  bool zero_pad = false;
 };
 
 // C[M,N] = epi(A[M,K] * B[N,K]^T); T in {float, __bf16}; OutT in {T, float}.
@@ -76,12 +78,23 @@ hipError_t launch_norm(const T* x, T* y, int M, int D, int mode, const float* p0
 // start at a multiple of the head width), times scale0 on segment 0,
 // then (rope != null) rotate consecutive pairs of each head_dim-wide head by
 // the token's 3D angles.
+// A descriptor without a table rotates nothing; it may bring a second set of
+// rows, of the same width and gain table, that the launch normalises beside the
+// first (nseg 1 only; unscaled, not rotated): rows1 rows from src1 (columns
+// through src_idx1, kept heads like gain_idx, when not null) to dst1, with gain
+// gain1.  dst1 may be src1.
 struct RopeDesc {
   const float* table;  // float2 (cos, sin) entries, see rope_table_size
   int L;               // tokens per sample (row % L = token)
   int gf, gh, gw;      // token grid
   int jt, jh, jw;      // pairs per axis
   int head_dim;
+  int rows1 = 0;
+  const void* src1 = nullptr;
+  void* dst1 = nullptr;
+  int64_t lds1 = 0, ldd1 = 0;
+  const int32_t* src_idx1 = nullptr;
+  const float* gain1 = nullptr;
 };
 template <typename T>
 hipError_t launch_qk_norm(T* buf, int64_t ld, int rows, int a, int nseg, int off0, int off1,
@@ -89,26 +102,16 @@ hipError_t launch_qk_norm(T* buf, int64_t ld, int rows, int a, int nseg, int off
                           const RopeDesc* rope, hipStream_t stream,
                           const int32_t* gain_idx = nullptr, float scale0 = 1.f);
 
-// Vt[(b*a + c)*ldvt + j] = src[(b*Lk + j)*lds + c] for j < Lk, 0 for Lk <= j < ldvt.
-template <typename T>
-hipError_t launch_transpose_vt(const T* src, int64_t lds, int a, int B, int Lk, T* Vt,
-                               int64_t ldvt, hipStream_t stream);
-
 // dst[r][c] = src[ridx[r]][cidx[c]] (identity when an index table is null,
 // zero when an index is negative).
 template <typename T>
 hipError_t launch_gather(const T* src, int64_t lds, T* dst, int64_t ldd, int rows, int cols,
                          const int32_t* ridx, const int32_t* cidx, hipStream_t stream);
 
-// 16-byte gathers of whole kept heads (idx groups of 16 / sizeof(T) entries
-// are aligned runs of consecutive channels):
-//   cols: dst[r][j] = src[r][idx[j]]                      r < rows, j < cols
-//   rows: dst[b*dst_bs + r*ld + :] = src[b*src_bs + idx[r]*ld + :]   r < rows, b < batches
+// 16-byte gather of rows:
+//   dst[b*dst_bs + r*ld + :] = src[b*src_bs + idx[r]*ld + :]   r < rows, b < batches
 // hipErrorInvalidValue when a width / stride is not a whole number of vectors
 // or a base pointer is not 16-byte aligned.
-template <typename T>
-hipError_t launch_gather_cols16(const T* src, int64_t lds, T* dst, int64_t ldd, int rows, int cols,
-                                const int32_t* idx, hipStream_t stream);
 template <typename T>
 hipError_t launch_gather_rows16(const T* src, int64_t src_bs, T* dst, int64_t dst_bs, int64_t ld,
                                 int rows, int batches, const int32_t* idx, hipStream_t stream);

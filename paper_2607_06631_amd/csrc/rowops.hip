@@ -1,5 +1,5 @@
 // HBM-bound row kernels for gfx950: LayerNorm + AdaLN modulation,
-// QK RMSNorm + 3D RoPE, V transpose, plan-time gather, timestep GEMV and
+// QK RMSNorm + 3D RoPE, plan-time gather, timestep GEMV and
 // small elementwise steps.  Rows are read once with 16-byte vector loads,
 // kept in registers between the statistics and the apply pass, and written
 // once; statistics are fp32 whatever the storage type.
@@ -230,16 +230,17 @@ constexpr int QK_WAVES = 8;    // 16 KB of loads in flight per wave; registers f
 // more rows' loads in flight (5.3 TB/s; 16 rows per wave, one workgroup per CU,
 // reached 4.2).  Two segments (q and k, twice the loads per row): 16 (5.4-5.5
 // TB/s against 5.3 with 4).  Below that 4 (two segments), then 1, the latter
-// with fewer waves per workgroup (row_split).
-template <int NSEG>
-constexpr int qk_rpw() { return NSEG == 2 ? 16 : 4; }
+// with fewer waves per workgroup (row_split).  (Rows of 16 chunks per lane: 1,
+// the registers of several spill.)
+template <int NSEG, int MAXC>
+constexpr int qk_rpw() { return NSEG == 2 ? 16 : MAXC > 12 ? 1 : 4; }
 template <typename T, int MAXC, int NSEG, int RPW>
 __global__ __launch_bounds__(64 * QK_WAVES) void qk_norm_kernel(T* buf, int64_t ld, int rows, int a,
                                                             int nseg, int off0, int off1,
                                                             const float* g0, const float* g1,
                                                             const int32_t* gidx, float scale0,
                                                             float inv_dim, float eps, RopeDesc rope,
-                                                            int vec) {
+                                                            int vec, int nb1) {
   constexpr int VEC = Chunk<T>::VEC;
   constexpr int NP = VEC / 2;  // pairs per chunk
   extern __shared__ float gain_lds[];  // [nseg][a]
@@ -247,15 +248,30 @@ __global__ __launch_bounds__(64 * QK_WAVES) void qk_norm_kernel(T* buf, int64_t 
   const int nch = a / VEC;
   const int jb = ((lane * VEC) % rope.head_dim) / 2;  // first head-local pair of this lane
   const int nwaves = blockDim.x >> 6;
-  const int64_t row0 = ((int64_t)blockIdx.x * nwaves + (threadIdx.x >> 6)) * RPW;
-  auto load_row = [&](int64_t row, u32x4 (&dst)[NSEG][MAXC]) {   // both segments' loads together
+  // the first nb1 workgroups take the descriptor's second row set (so its few
+  // rows do not end the launch), the others the rows of buf, in place
+  const bool second = NSEG == 1 && (int)blockIdx.x < nb1;
+  const int64_t row0 = ((int64_t)(blockIdx.x - (second ? 0 : nb1)) * nwaves + (threadIdx.x >> 6)) * RPW;
+  const T* src = second ? static_cast<const T*>(rope.src1) : buf;
+  const int64_t lds = second ? rope.lds1 : ld;
+  const int32_t* sidx = second ? rope.src_idx1 : nullptr;
+  if (second) {
+    rows = rope.rows1;
+    g0 = rope.gain1;
+    scale0 = 1.f;
+  }
+  // both segments' loads of a row together (idx: columns of the second set)
+  auto load_row = [&](int64_t row, u32x4 (&to)[NSEG][MAXC], const int32_t* idx) __attribute__((always_inline)) {
 #pragma unroll
     for (int sg = 0; sg < NSEG; ++sg) {
-      const T* xr = buf + row * ld + (sg == 0 ? off0 : off1);
+      const T* xr = src + row * lds + (sg == 0 ? off0 : off1);
 #pragma unroll
       for (int i = 0; i < MAXC; ++i) {
         const int c = lane + kWave * i;
-        if (c < nch) dst[sg][i] = *reinterpret_cast<const u32x4*>(xr + c * VEC);
+        if (c < nch) {
+          const int at = idx ? idx[c * VEC] : c * VEC;
+          to[sg][i] = *reinterpret_cast<const u32x4*>(xr + at);
+        }
       }
     }
   };
@@ -264,7 +280,7 @@ __global__ __launch_bounds__(64 * QK_WAVES) void qk_norm_kernel(T* buf, int64_t 
   // with a run-time count the wide two-segment launch took 312 us, not 170)
   u32x4 lone[NSEG][MAXC];
   if constexpr (RPW == 1) {
-    if (row0 < rows) load_row(row0, lone);
+    if (row0 < rows) load_row(row0, lone, sidx);
   }
   auto ld4 = [](const float* p) { return *reinterpret_cast<const f32x4*>(p); };
   if (vec) {   // 16-byte gain loads (a is whole heads, and so are the runs of a gain table)
@@ -289,12 +305,7 @@ __global__ __launch_bounds__(64 * QK_WAVES) void qk_norm_kernel(T* buf, int64_t 
     }
   }
   __syncthreads();
-  for (int rr = 0; rr < RPW; ++rr) {
-    const int64_t row = row0 + rr;
-    if (row >= rows) break;
-    u32x4 own[NSEG][MAXC];
-    if constexpr (RPW > 1) load_row(row, own);
-    u32x4(&raw)[NSEG][MAXC] = RPW > 1 ? own : lone;
+  auto work = [&](int64_t row, const u32x4 (&raw)[NSEG][MAXC], T* dst, int64_t ldd) __attribute__((always_inline)) {
     // rotation factors of this lane's pairs (table reads overlap the loads)
     float cs[NP], sn[NP];
     if (rope.table) {
@@ -333,7 +344,7 @@ __global__ __launch_bounds__(64 * QK_WAVES) void qk_norm_kernel(T* buf, int64_t 
     }
 #pragma unroll
     for (int sg = 0; sg < NSEG; ++sg) {
-      T* xr = buf + row * ld + (sg == 0 ? off0 : off1);
+      T* xr = dst + row * ldd + (sg == 0 ? off0 : off1);
       const float* gain = gain_lds + sg * a;
 #pragma unroll
       for (int i = 0; i < MAXC; ++i) {
@@ -360,6 +371,27 @@ __global__ __launch_bounds__(64 * QK_WAVES) void qk_norm_kernel(T* buf, int64_t 
         }
       }
     }
+  };
+  if constexpr (RPW == 1) {
+    if (row0 < rows)
+      work(row0, lone, second ? static_cast<T*>(rope.dst1) : buf, second ? rope.ldd1 : ld);
+  } else {
+    if (NSEG == 1 && second) {
+#pragma unroll 1   // (few rows; the loop below sets the kernel's registers)
+      for (int rr = 0; rr < RPW; ++rr) {
+        u32x4 raw[NSEG][MAXC];
+        if (row0 + rr >= rows) break;
+        load_row(row0 + rr, raw, sidx);
+        work(row0 + rr, raw, static_cast<T*>(rope.dst1), rope.ldd1);
+      }
+      return;
+    }
+    for (int rr = 0; rr < RPW; ++rr) {
+      u32x4 raw[NSEG][MAXC];
+      if (row0 + rr >= rows) break;
+      load_row(row0 + rr, raw, nullptr);
+      work(row0 + rr, raw, buf, ld);
+    }
   }
 }
 
@@ -374,24 +406,36 @@ hipError_t launch_qk_norm(T* buf, int64_t ld, int rows, int a, int nseg, int off
   if (rd.head_dim <= 0) rd.head_dim = 64;   // no rotation: any width dividing 64 * VEC
   constexpr int VEC = Chunk<T>::VEC;
   if ((64 * VEC) % rd.head_dim != 0) return hipErrorInvalidValue;
-  const int vec = aligned16({g0, g1});
+  const int vec = aligned16({g0, g1, rd.gain1});
+  if (rd.rows1 > 0 && (nseg != 1 || rd.table || !rd.src1 || !rd.dst1 || !rd.gain1 ||
+                       !aligned16({rd.src1, rd.dst1}) || rd.lds1 % VEC || rd.ldd1 % VEC))
+    return hipErrorInvalidValue;
   // q and k in one launch while both fit the registers (up to 8 chunks per
   // lane), else one launch per segment
   auto launch = [&](auto c_tag, auto nseg_tag, int off_a, int off_b, const float* ga,
                     const float* gb, float sa) {
     constexpr int C = decltype(c_tag)::value, NS = decltype(nseg_tag)::value;
-    const RowSplit rs = row_split(rows, QK_WAVES, qk_rpw<NS>());
+    const RowSplit rs = row_split(rows, QK_WAVES, qk_rpw<NS, C>());
     auto go = [&](auto rpw_tag) {
       constexpr int RPW = decltype(rpw_tag)::value;
       const int rows_per_wg = rs.waves * RPW;
-      const dim3 grid((rows + rows_per_wg - 1) / rows_per_wg);
+      const int nb1 = (rd.rows1 + rows_per_wg - 1) / rows_per_wg;
+      const dim3 grid((rows + rows_per_wg - 1) / rows_per_wg + nb1);
       hipLaunchKernelGGL((qk_norm_kernel<T, C, NS, RPW>), grid, dim3(64 * rs.waves),
                          NS * a * sizeof(float), stream, buf, ld, rows, a, NS, off_a, off_b, ga, gb,
-                         gain_idx, sa, inv_norm_dim, eps, rd, vec);
+                         gain_idx, sa, inv_norm_dim, eps, rd, vec, nb1);
     };
-    if (rs.rpw == qk_rpw<NS>()) go(std::integral_constant<int, qk_rpw<NS>()>{});
-    else if (NS == 2 && rs.rpw >= 4) go(std::integral_constant<int, 4>{});
-    else go(std::integral_constant<int, 1>{});
+    if (rs.rpw == qk_rpw<NS, C>()) {
+      go(std::integral_constant<int, qk_rpw<NS, C>()>{});
+      return;
+    }
+    if constexpr (NS == 2) {
+      if (rs.rpw >= 4) {
+        go(std::integral_constant<int, 4>{});
+        return;
+      }
+    }
+    go(std::integral_constant<int, 1>{});
   };
   auto by_chunks = [&](auto c_tag) {
     constexpr int C = decltype(c_tag)::value;
@@ -415,83 +459,6 @@ hipError_t launch_qk_norm(T* buf, int64_t ld, int rows, int a, int nseg, int off
     case 16: by_chunks(std::integral_constant<int, 16>{}); break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// V -> V^T per sample, 64 x 64 tiles through LDS, zero-filled key padding
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(R_THREADS) void transpose_vt_kernel(const T* __restrict__ src,
-                                                                 int64_t lds, int a, int Lk,
-                                                                 T* __restrict__ vt, int64_t ldvt) {
-  __shared__ float tile[64][65];
-  const int j0 = blockIdx.x * 64, c0 = blockIdx.y * 64, b = blockIdx.z;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int jj = ty; jj < 64; jj += R_WAVES) {
-    const int j = j0 + jj, c = c0 + tx;
-    float v = 0.f;
-    if (j < Lk && c < a) v = to_f32(src[((int64_t)b * Lk + j) * lds + c]);
-    tile[jj][tx] = v;
-  }
-  __syncthreads();
-  for (int cc = ty; cc < 64; cc += R_WAVES) {
-    const int c = c0 + cc, j = j0 + tx;
-    if (c < a && j < ldvt) vt[((int64_t)b * a + c) * ldvt + j] = from_f32<T>(tile[tx][cc]);
-  }
-}
-
-// bf16: a lane moves an 8-token x 8-channel block: eight 16-byte loads of
-// token rows, a register transpose (v_perm_b32 pairs 16-bit halves of two
-// token rows; the rest is register renaming) and eight 16-byte stores of
-// channel rows.  Lanes (cx, ty) of a wave: 8 lanes read 128 contiguous
-// bytes of a token row and 8 lanes write 128 contiguous bytes of a V^T row.
-// Tokens past Lk are written as zeros up to ldvt (a multiple of 8).
-__global__ __launch_bounds__(R_THREADS) void transpose_vt8_kernel(const bf16* __restrict__ src,
-                                                                  int64_t lds, int a, int Lk,
-                                                                  bf16* __restrict__ vt,
-                                                                  int64_t ldvt) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cx = lane & 7, ty = lane >> 3;
-  const int c0 = blockIdx.y * 64 + cx * 8;                        // first channel
-  const int64_t t0 = ((int64_t)blockIdx.x * R_WAVES + wave) * 64 + ty * 8;   // first token
-  const int b = blockIdx.z;
-  if (t0 >= ldvt || c0 >= a) return;
-  uint32_t in[8][4];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    u32x4 v = u32x4{0u, 0u, 0u, 0u};
-    if (t0 + r < Lk) v = *reinterpret_cast<const u32x4*>(src + ((int64_t)b * Lk + t0 + r) * lds + c0);
-#pragma unroll
-    for (int d = 0; d < 4; ++d) in[r][d] = v[d];
-  }
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const int d = c >> 1;
-    const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;    // high or low halves
-    u32x4 o;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = __builtin_amdgcn_perm(in[2 * k + 1][d], in[2 * k][d], sel);
-    *reinterpret_cast<u32x4*>(vt + ((int64_t)b * a + c0 + c) * ldvt + t0) = o;
-  }
-}
-
-template <typename T>
-hipError_t launch_transpose_vt(const T* src, int64_t lds, int a, int B, int Lk, T* Vt,
-                               int64_t ldvt, hipStream_t stream) {
-  if (a <= 0 || B <= 0) return hipSuccess;
-  if constexpr (sizeof(T) == 2) {
-    if (a % 64 == 0 && ldvt % 8 == 0 && lds % 8 == 0 &&
-        reinterpret_cast<uintptr_t>(src) % 16 == 0 && reinterpret_cast<uintptr_t>(Vt) % 16 == 0) {
-      dim3 grid((unsigned)((ldvt + 64 * R_WAVES - 1) / (64 * R_WAVES)), (unsigned)(a / 64), (unsigned)B);
-      hipLaunchKernelGGL(transpose_vt8_kernel, grid, dim3(R_THREADS), 0, stream, src, lds, a, Lk, Vt,
-                         ldvt);
-      return hipGetLastError();
-    }
-  }
-  dim3 grid((unsigned)((ldvt + 63) / 64), (unsigned)((a + 63) / 64), (unsigned)B);
-  hipLaunchKernelGGL((transpose_vt_kernel<T>), grid, dim3(R_THREADS), 0, stream, src, lds, a, Lk,
-                     Vt, ldvt);
   return hipGetLastError();
 }
 
@@ -620,28 +587,9 @@ hipError_t launch_gather(const T* src, int64_t lds, T* dst, int64_t ldd, int row
 }
 
 // ---------------------------------------------------------------------------
-// Kept heads of the cached text projections, 16 bytes per lane.  A kept head
-// is head_dim consecutive channels starting at a multiple of head_dim, so
-// every aligned group of V = 16 / sizeof(T) table entries is one contiguous,
-// aligned 16-byte vector of the source.
-//   cols: dst[r, j] = src[r, idx[j]]              (r < rows, j < cols)
-//   rows: dst[b, r, :] = src[b, idx[r], :]        (r < rows, n per row)
+// Kept heads of the cached V^T, 16 bytes per lane:
+//   dst[b, r, :] = src[b, idx[r], :]        (r < rows, n per row)
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(R_THREADS) void gather_cols16_kernel(const T* __restrict__ src,
-                                                                  int64_t lds, T* __restrict__ dst,
-                                                                  int64_t ldd, int64_t total, int nvec,
-                                                                  const int32_t* __restrict__ idx) {
-  constexpr int V = 16 / sizeof(T);
-  const int64_t i = (int64_t)blockIdx.x * R_THREADS + threadIdx.x;
-  if (i >= total) return;
-  const int64_t r = i / nvec;
-  const int q = (int)(i - r * nvec);
-  const int sc = idx[q * V];
-  *reinterpret_cast<u32x4*>(dst + r * ldd + (int64_t)q * V) =
-      *reinterpret_cast<const u32x4*>(src + r * lds + sc);
-}
-
 template <typename T>
 __global__ __launch_bounds__(R_THREADS) void gather_rows16_kernel(const T* __restrict__ src,
                                                                   int64_t src_bs, T* __restrict__ dst,
@@ -655,20 +603,6 @@ __global__ __launch_bounds__(R_THREADS) void gather_rows16_kernel(const T* __res
   const int64_t b = blockIdx.y;
   *reinterpret_cast<u32x4*>(dst + b * dst_bs + r * ld + q * V) =
       *reinterpret_cast<const u32x4*>(src + b * src_bs + (int64_t)idx[r] * ld + q * V);
-}
-
-template <typename T>
-hipError_t launch_gather_cols16(const T* src, int64_t lds, T* dst, int64_t ldd, int rows, int cols,
-                                const int32_t* idx, hipStream_t stream) {
-  constexpr int V = 16 / sizeof(T);
-  if (rows <= 0 || cols <= 0) return hipSuccess;
-  if (cols % V || lds % V || ldd % V || reinterpret_cast<uintptr_t>(src) % 16 ||
-      reinterpret_cast<uintptr_t>(dst) % 16)
-    return hipErrorInvalidValue;
-  const int64_t total = (int64_t)rows * (cols / V);
-  hipLaunchKernelGGL((gather_cols16_kernel<T>), dim3((unsigned)((total + R_THREADS - 1) / R_THREADS)),
-                     dim3(R_THREADS), 0, stream, src, lds, dst, ldd, total, cols / V, idx);
-  return hipGetLastError();
 }
 
 template <typename T>
@@ -827,12 +761,8 @@ hipError_t launch_cast(const float* src, T* dst, int64_t n, hipStream_t stream) 
   template hipError_t launch_qk_norm<T>(T*, int64_t, int, int, int, int, int, const float*,    \
                                         const float*, float, float, const RopeDesc*,           \
                                         hipStream_t, const int32_t*, float);                   \
-  template hipError_t launch_transpose_vt<T>(const T*, int64_t, int, int, int, T*, int64_t,    \
-                                             hipStream_t);                                     \
   template hipError_t launch_gather<T>(const T*, int64_t, T*, int64_t, int, int,               \
                                        const int32_t*, const int32_t*, hipStream_t);           \
-  template hipError_t launch_gather_cols16<T>(const T*, int64_t, T*, int64_t, int, int,        \
-                                              const int32_t*, hipStream_t);                    \
   template hipError_t launch_gather_rows16<T>(const T*, int64_t, T*, int64_t, int64_t, int, int,\
                                               const int32_t*, hipStream_t);                    \
   template hipError_t launch_gemv<T>(const T*, const float*, const float*, float*, int, int,   \
