@@ -1,10 +1,10 @@
 // Bidirectional flash attention on MFMA for gfx950.
 //
-// Three kernels share one arithmetic: bf16 with head_dim 128 on long key
+// Two kernels share one arithmetic: bf16 with head_dim 128 on long key
 // sequences (the blocks' self-attention) runs flash_attn_g2_kernel, four
-// waves of two 32-query groups each (below); the other long-key cases run
-// the eight-wave flash_attn_kernel, short key sequences (text tokens) and
-// float32 the four-wave one.
+// waves of two 32-query groups each (below); the other cases run
+// flash_attn_kernel, with eight or four waves of 32 queries per key tile (two for
+// float32, with two key groups).
 //
 // Work split of flash_attn_kernel: one workgroup = 8 waves of one (sample,
 // head); a wave owns 32 queries and walks all keys in tiles of 64, as two
@@ -142,10 +142,20 @@ __device__ __forceinline__ void store_rows_staged(const f32x16 (&o)[DH / 32], fl
   }
 }
 
-// SC: queries arrive pre-multiplied by log2(e)/sqrt(dh); AT_WAVES waves per
-// workgroup (4 or 8: two waves per SIMD either way).
-template <typename T, int DH, bool SC, int AT_WAVES>
-__global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel(AttnParams<T> p) {
+// SC: queries arrive pre-multiplied by log2(e)/sqrt(dh).  NQ groups of 32
+// queries times NK key groups of waves per workgroup (4 or 8 waves: two per SIMD
+// either way), tiles of BN keys.
+//
+// NK > 1, for problems with too few query blocks to fill the chip: the keys are
+// cut into NK ranges of whole tiles, each walked by its own NQ waves with tiles
+// of their own in LDS, and the ranges' sums are merged through LDS at the end
+// (O = sum a_k O_k / sum a_k l_k, a_k = 2^(m_k - max m)).  A wave's serial chain
+// of tiles is then NK times shorter and a workgroup has fewer queries, with
+// nothing written to memory in between.
+template <typename T, int DH, bool SC, int NQ, int NK, int BN>
+__global__ __launch_bounds__(64 * NQ * NK, 8 / (NQ * NK)) void flash_attn_kernel(AttnParams<T> p) {
+  constexpr int AT_BN = BN;
+  constexpr int AT_WAVES = NQ;                      // waves that share a tile
   constexpr int AT_THREADS = 64 * AT_WAVES;
   constexpr int VEC = Chunk<T>::VEC;
   constexpr int KCH = DH * (int)sizeof(T) / 16;     // chunks per K row
@@ -157,10 +167,11 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
   constexpr int BMQ = AT_WAVES * 32;                // queries per workgroup
   static_assert(K_PER_T * AT_THREADS == AT_BN * KCH, "K tile split");
   static_assert(V_PER_T * AT_THREADS == DH * VCH, "V tile split");
-  __shared__ u32x4 ks_[2][AT_BN][KCH];
-  __shared__ u32x4 vs_[2][DH][VCH];
+  __shared__ u32x4 ks_[NK][2][AT_BN][KCH];
+  __shared__ u32x4 vs_[NK][2][DH][VCH];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int kg = NK == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / AT_THREADS);   // key group
+  const int tid = (int)threadIdx.x - kg * AT_THREADS, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 5, col = lane & 31;
 
   const int nqb = (p.Lq + BMQ - 1) / BMQ;
@@ -175,6 +186,11 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
     split = sidx;
     if (sidx & 1) t0 = p.split_tile;
     else t1 = p.split_tile;
+  }
+  const int per = (ntiles + NK - 1) / NK;   // tiles of a key group
+  if constexpr (NK > 1) {
+    t0 = min(kg * per, ntiles);
+    t1 = min(t0 + per, ntiles);
   }
   const int qb = bid % nqb, hb = bid / nqb;
   const int h = hb % p.H, b = hb / p.H;
@@ -221,13 +237,13 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
     vd_off[j] = (uint32_t)((d * p.ldvt + swz<VCH>(d, lane % VCH) * VEC) * ES);
   }
   const int64_t v_bytes = (int64_t)DH * p.ldvt * ES;
-  auto k_rsrc = [&](int key0) {
+  auto k_rsrc = [&](int key0) __attribute__((always_inline)) {
     const int64_t kb = (int64_t)(p.Lk - key0) * p.ldk * ES;
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(kbase + (int64_t)key0 * p.ldk), (short)0,
                                              (uint32_t)(kb < 0xffffffffll ? kb : 0xffffffffll),
                                              kRsrcWord3);
   };
-  auto load_direct = [&](int kt, int buf) {
+  auto load_direct = [&](int kt, int buf) __attribute__((always_inline)) {
 #if defined(__HIP_DEVICE_COMPILE__)
     typedef __attribute__((address_space(3))) void lds_t;
     const int key0 = kt * AT_BN;
@@ -236,16 +252,16 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
         const_cast<T*>(vbase + key0), (short)0, (uint32_t)(v_bytes - (int64_t)key0 * ES), kRsrcWord3);
 #pragma unroll
     for (int j = 0; j < KI; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lds_t*)&ks_[buf][(j * AT_WAVES + wave) * KRPI][0], 16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lds_t*)&ks_[kg][buf][(j * AT_WAVES + wave) * KRPI][0], 16,
                                                kd_off[j], 0, 0, 0);
 #pragma unroll
     for (int j = 0; j < VI; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_t*)&vs_[buf][(j * AT_WAVES + wave) * VRPI][0], 16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_t*)&vs_[kg][buf][(j * AT_WAVES + wave) * VRPI][0], 16,
                                                vd_off[j], 0, 0, 0);
 #endif
   };
   // tail tile: through registers, V^T zero-filled past Lk
-  auto load_tail = [&](int kt, int buf) {
+  auto load_tail = [&](int kt, int buf) __attribute__((always_inline)) {
     const int key0 = kt * AT_BN;
     const __amdgpu_buffer_rsrc_t kr = k_rsrc(key0);
 #pragma unroll
@@ -255,7 +271,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
       const u32x4 v = __builtin_bit_cast(
           u32x4, __builtin_amdgcn_raw_buffer_load_b128(kr, (uint32_t)((kl * p.ldk + c * VEC) * ES), 0, 0));
       const int row = (kl & ~31) + key_slot(kl & 31);
-      ks_[buf][row][swz<KCH>(row, c)] = v;
+      ks_[kg][buf][row][swz<KCH>(row, c)] = v;
     }
 #pragma unroll
     for (int i = 0; i < V_PER_T; ++i) {
@@ -270,10 +286,10 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
           if (k0 + e >= p.Lk) tmp[e] = 0.f;
         v = Chunk<T>::pack(tmp);
       }
-      vs_[buf][d][swz<VCH>(d, c)] = v;
+      vs_[kg][buf][d][swz<VCH>(d, c)] = v;
     }
   };
-  auto load_tile = [&](int kt, int buf) {
+  auto load_tile = [&](int kt, int buf) __attribute__((always_inline)) {
     if ((kt + 1) * AT_BN <= p.Lk) load_direct(kt, buf);
     else load_tail(kt, buf);
   };
@@ -288,7 +304,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
 
   // S^T of half kk of the tile in buffer buf, plus c0 (an accumulator
   // initialiser); K fragments are read in batches of KB ahead of their MFMAs.
-  auto scores = [&](int buf, int kk, const f32x16& c0) {
+  auto scores = [&](int buf, int kk, const f32x16& c0) __attribute__((always_inline)) {
     constexpr int KB = NQS >= 8 ? NQS / 2 : NQS;
     f32x16 s = c0;
     __builtin_amdgcn_sched_barrier(0);
@@ -297,7 +313,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
     for (int s0 = 0; s0 < NQS; s0 += KB) {
       u32x4 kf[KB];
 #pragma unroll
-      for (int st = 0; st < KB; ++st) kf[st] = ks_[buf][kk * 32 + col][swz<KCH>(col, 2 * (s0 + st) + g)];
+      for (int st = 0; st < KB; ++st) kf[st] = ks_[kg][buf][kk * 32 + col][swz<KCH>(col, 2 * (s0 + st) + g)];
 #pragma unroll
       for (int st = 0; st < KB; ++st) Mma<T>::step(s, kf[st], qf[s0 + st]);
     }
@@ -305,21 +321,22 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
     __builtin_amdgcn_s_setprio(0);
     return s;
   };
-  auto mask = [&](f32x16& s, int key) {   // keys >= Lk -> -inf
+  auto mask = [&](f32x16& s, int key) __attribute__((always_inline)) {   // keys >= Lk -> -inf
 #pragma unroll
     for (int r = 0; r < 16; ++r)
       if (key + 16 * g + r >= p.Lk) s[r] = -INFINITY;
   };
 
-  load_tile(t0, 0);
+  const bool any = NK == 1 || t0 < t1;   // (a key group may have no keys)
+  if (any) load_tile(t0, 0);
   wait_vmcnt<0>();   // this wave's direct-to-LDS loads have landed
   __syncthreads();   // ... and every other wave's
 
   // Initial base: the max of each query's first 32 scores of the range (its
   // first key exists, so it is finite).  negm holds -m in MFMA output units.
-  float m_run;
+  float m_run = -INFINITY;
   f32x16 negm;
-  {
+  if (any) {
     f32x16 z;
 #pragma unroll
     for (int r = 0; r < 16; ++r) z[r] = 0.f;
@@ -336,16 +353,16 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
   // One key tile.  The LDS buffer and whether the tile needs the key-tail
   // masks are compile-time, so fragment addresses are lane constants plus
   // immediate offsets and full tiles carry no masking code.
-  auto tile = [&](int kt, auto buf_c, auto masked_c) {
+  auto tile = [&](int kt, auto buf_c, auto masked_c) __attribute__((always_inline)) {
     constexpr int buf = decltype(buf_c)::value;
     constexpr bool MASKED = decltype(masked_c)::value;
     // buffer buf^1 was last read before the previous barrier
     if (kt + 1 < t1) load_tile(kt + 1, buf ^ 1);
 
     const int key0 = kt * AT_BN;
-    // the two 32-key halves of the tile in turn: S^T, softmax, O^T += V^T P^T
+    // the 32-key halves of the tile in turn: S^T, softmax, O^T += V^T P^T
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
+    for (int kk = 0; kk < BN / 32; ++kk) {
       __builtin_amdgcn_sched_barrier(0);   // halves are not interleaved (register budget)
       f32x16 s = scores(buf, kk, negm);   // (scores - m) in MFMA output units
       // (the tail tile masks before its V^T reads: fewer registers live
@@ -357,7 +374,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
       for (int u = 0; u < NPC; ++u)
 #pragma unroll
         for (int dt = 0; dt < DH / 32; ++dt)
-          vf[u][dt] = vs_[buf][dt * 32 + col][swz<VCH>(col, (kk * 32 + 16 * g) / VEC + u)];
+          vf[u][dt] = vs_[kg][buf][dt * 32 + col][swz<VCH>(col, (kk * 32 + 16 * g) / VEC + u)];
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!SC) {
 #pragma unroll
@@ -367,7 +384,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
       // O^T += V^T P^T, and this half's lane-partial row sum
       u32x4 pc[NPC];
       float lh = 0.f;
-      auto probs = [&]() {
+      auto probs = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < NPC; ++u) {
           float pv[VEC];
@@ -428,7 +445,7 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
   using B0 = std::integral_constant<int, 0>;
   using B1 = std::integral_constant<int, 1>;
   const int nfull = min(p.Lk / AT_BN, t1);   // tiles of 64 valid keys in the range
-  int kt = t0;   // (t0 is even: buffer 0 holds tile t0)
+  int kt = t0;   // (buffer 0 holds tile t0)
   for (; kt + 2 <= nfull; kt += 2) {
     tile(kt, B0{}, std::false_type{});
     tile(kt + 1, B1{}, std::false_type{});
@@ -438,8 +455,12 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
     if ((kt - t0) & 1) tile(kt, B1{}, std::true_type{});
     else tile(kt, B0{}, std::true_type{});
   }
+  if constexpr (NK > 1) {
+    // a group with fewer tiles joins the others' barriers
+    for (int i = t1 - t0; i < per; ++i) __syncthreads();
+  }
 
-  const float l = l_run + __shfl_xor(l_run, 32);
+  float l = l_run + __shfl_xor(l_run, 32);
   if (split >= 0) {
     // unnormalised sums and this half's (m, l), combined by attn_merge_kernel
     const int nsplit = (int)(gridDim.x - p.nreg) / 2;
@@ -465,16 +486,80 @@ __global__ __launch_bounds__(64 * AT_WAVES, 8 / AT_WAVES) void flash_attn_kernel
   // holds four consecutive dims of its query per register group, so direct
   // stores would put 32 rows in every store instruction; staged, each
   // instruction writes whole rows (full 128-byte lines).
+  if constexpr (NK > 1) {
+    // key groups 1.. leave their sums in LDS (every wave is past its last tile):
+    // [group, query group][float4 of the accumulators][lane], then m and l
+    constexpr int NF = DH / 8;   // float4s per lane
+    // (the two arrays in turn: a slot is one wave's float4s)
+    constexpr int SLOT = 64 * NF;                                   // u32x4 per wave
+    constexpr int KS = (int)(sizeof(ks_) / 16) / (SLOT + 32);   // slots that fit the K tiles
+    auto slot = [&](int g1) __attribute__((always_inline)) -> u32x4* {
+      const int i = (g1 - 1) * NQ + wave;
+      return i < KS ? &ks_[0][0][0][0] + i * (SLOT + 32) : &vs_[0][0][0][0] + (i - KS) * (SLOT + 32);
+    };
+    static_assert((NK - 1) * NQ <= KS + (int)(sizeof(vs_) / 16) / (SLOT + 32), "merge slots");
+    if (kg > 0) {
+      u32x4* d = slot(kg);
+#pragma unroll
+      for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = o[dt][4 * rr + e];
+          d[(dt * 4 + rr) * 64 + lane] = __builtin_bit_cast(u32x4, v);
+        }
+      float* ml = reinterpret_cast<float*>(d + SLOT);
+      ml[lane] = m_run;
+      ml[64 + lane] = l;
+    }
+    __syncthreads();
+    if (kg == 0) {
+      float mx = m_run, mk[NK], a[NK];
+      mk[0] = m_run;
+#pragma unroll
+      for (int k = 1; k < NK; ++k) {
+        mk[k] = reinterpret_cast<const float*>(slot(k) + SLOT)[lane];
+        mx = fmaxf(mx, mk[k]);
+      }
+      // (group 0 has keys, so mx is finite; an empty group's 2^-inf is zero)
+#pragma unroll
+      for (int k = 0; k < NK; ++k) a[k] = __builtin_amdgcn_exp2f(mk[k] - mx);
+      l *= a[0];
+#pragma unroll
+      for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] *= a[0];
+#pragma unroll
+      for (int k = 1; k < NK; ++k) {
+        const u32x4* d = slot(k);
+        l += a[k] * reinterpret_cast<const float*>(d + SLOT)[64 + lane];
+#pragma unroll
+        for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr) {
+            const f32x4 v = __builtin_bit_cast(f32x4, d[(dt * 4 + rr) * 64 + lane]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[dt][4 * rr + e] += a[k] * v[e];
+          }
+        __builtin_amdgcn_sched_barrier(0);   // (one group's sums in registers at a time)
+      }
+    }
+    __syncthreads();   // (the staging below reuses this space)
+    if (kg > 0) return;
+  }
   const float inv = 1.f / l;
-  store_rows_staged<T, DH>(o, inv, wave < 4 ? reinterpret_cast<char*>(&ks_[0][0][0]) + wave * 32 * DH * (int)sizeof(T)
-                                             : reinterpret_cast<char*>(&vs_[0][0][0]) + (wave - 4) * 32 * DH * (int)sizeof(T),
+  store_rows_staged<T, DH>(o, inv, wave < 4 ? reinterpret_cast<char*>(&ks_[0][0][0][0]) + wave * 32 * DH * (int)sizeof(T)
+                                             : reinterpret_cast<char*>(&vs_[0][0][0][0]) + (wave - 4) * 32 * DH * (int)sizeof(T),
                            p.O + ((int64_t)b * p.Lq + qb * BMQ + wave * 32) * p.ldo + h * DH, p.ldo,
                            min(32, p.Lq - (qb * BMQ + wave * 32)), lane);
 }
 
 // Combines the two key halves of each split item: with m = max(m0, m1) and
-// a_k = 2^(m_k - m), O = (a0 O0 + a1 O1) / (a0 l0 + a1 l1).  One workgroup
-// per split item, a thread per four output dims of a query.
+// a_k = 2^(m_k - m), O = (a0 O0 + a1 O1) / (a0 l0 + a1 l1).  A workgroup per 32
+// queries of a split item (one per item left a wave 32 turns of a memory round
+// trip each: 16 us for 128 items), a thread per four output dims of a query.
+constexpr int MERGE_Q = 32;
 template <typename T, int DH, int BMQ>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams<T> p, int nsplit) {
   const int sidx = blockIdx.x;
@@ -482,8 +567,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams<T> p, int ns
   const int item = p.nreg + sidx;
   const int qb = item % nqb, hb = item / nqb;
   const int h = hb % p.H, b = hb / p.H;
-  for (int idx = threadIdx.x; idx < BMQ * DH / 4; idx += 256) {
-    const int ql = idx / (DH / 4), d = (idx % (DH / 4)) * 4;
+#pragma unroll
+  for (int idx = threadIdx.x; idx < MERGE_Q * DH / 4; idx += 256) {
+    const int ql = blockIdx.y * MERGE_Q + idx / (DH / 4), d = (idx % (DH / 4)) * 4;
     const int q = qb * BMQ + ql;
     if (q >= p.Lq) continue;
     const float* ml0 = p.part + part_ml_off<DH>(nsplit, sidx, 0, ql, BMQ);
@@ -1141,7 +1227,7 @@ void launch_g2(AttnParams<bf16> p, hipStream_t stream, int ncu) {
   p.split_tile = (nfull / 2) & ~1;
   hipLaunchKernelGGL((flash_attn_g2_kernel<SC>), dim3(p.nreg + 2 * nsplit), dim3(256), 0, stream, p);
   if (nsplit > 0)
-    hipLaunchKernelGGL((attn_merge_kernel<bf16, 128, BMQ>), dim3(nsplit), dim3(256), 0, stream, p, nsplit);
+    hipLaunchKernelGGL((attn_merge_kernel<bf16, 128, BMQ>), dim3(nsplit, BMQ / MERGE_Q), dim3(256), 0, stream, p, nsplit);
 }
 
 template <typename T, int DH, int W>
@@ -1162,28 +1248,73 @@ void launch_w(AttnParams<T> p, bool q_scaled, hipStream_t stream, int ncu) {
   p.split_tile = (nfull / 2) & ~1;
   const int blocks = p.nreg + 2 * nsplit;
   if (q_scaled)
-    hipLaunchKernelGGL((flash_attn_kernel<T, DH, true, W>), dim3(blocks), dim3(64 * W), 0, stream, p);
+    hipLaunchKernelGGL((flash_attn_kernel<T, DH, true, W, 1, AT_BN>), dim3(blocks), dim3(64 * W), 0, stream, p);
   else
-    hipLaunchKernelGGL((flash_attn_kernel<T, DH, false, W>), dim3(blocks), dim3(64 * W), 0, stream, p);
+    hipLaunchKernelGGL((flash_attn_kernel<T, DH, false, W, 1, AT_BN>), dim3(blocks), dim3(64 * W), 0, stream, p);
   if (nsplit > 0)
-    hipLaunchKernelGGL((attn_merge_kernel<T, DH, BMQ>), dim3(nsplit), dim3(256), 0, stream, p, nsplit);
+    hipLaunchKernelGGL((attn_merge_kernel<T, DH, BMQ>), dim3(nsplit, BMQ / MERGE_Q), dim3(256), 0, stream, p, nsplit);
+}
+
+// Two query groups and two key groups of 32-key tiles (no key split across
+// workgroups).
+template <typename T, int DH>
+void launch_groups(AttnParams<T> p, bool q_scaled, hipStream_t stream) {
+  constexpr int NQ = 2, NK = 2, BN = 32;
+  p.nreg = ((p.Lq + NQ * 32 - 1) / (NQ * 32)) * p.H * p.B;
+  if (q_scaled)
+    hipLaunchKernelGGL((flash_attn_kernel<T, DH, true, NQ, NK, BN>), dim3(p.nreg), dim3(64 * NQ * NK), 0,
+                       stream, p);
+  else
+    hipLaunchKernelGGL((flash_attn_kernel<T, DH, false, NQ, NK, BN>), dim3(p.nreg), dim3(64 * NQ * NK), 0,
+                       stream, p);
+}
+
+// Whether the two-group kernel is the faster one for fewer keys than
+// kLongKeys.  A 64-key tile costs it 1.7 us per round of a workgroup (256
+// queries) on every CU, half a round when the last one is split; the four-wave
+// kernel takes 2.27 us for as many queries, but in steps of 128 queries.  (3600
+// tokens, 40 heads: 263 us split, 294 four-wave, 298 unsplit.)  Only where the
+// four-wave kernel needs more than one round itself: with 27 heads of 1560
+// tokens, 49 against 51 us repeated on the same tensors but 68 against 62 in a
+// block, whose keys are not in the L2 yet and which a lone round does not hide.
+template <typename T>
+bool prefer_g2(const AttnParams<T>& p, int ncu) {
+  constexpr int kChip = 256;
+  const float four = (float)(((p.Lq + 127) / 128) * p.H * p.B) / (2 * kChip);
+  if (p.Lk < 2048 || four <= 1.f) return false;
+  const int items = ((p.Lq + 255) / 256) * p.H * p.B, rem = items % kChip;
+  const bool split = p.part && ncu > 0 && rem > 0 && 2 * rem <= ncu && rem <= kMaxSplitItems;
+  const float rounds = (float)(items / kChip) + (rem == 0 ? 0.f : split ? 0.5f : 1.f);
+  const float nt = (float)((p.Lk + 63) / 64);
+  return 1.03f * (nt * 1.7f * rounds + (split ? 16.f : 8.f)) < nt * 2.27f * four;
 }
 
 template <typename T, int DH>
 void launch_dh(const AttnParams<T>& p, bool q_scaled, hipStream_t stream, int ncu) {
-  // (float32 keeps four waves: its head-128 kernel needs one wave per SIMD)
   if constexpr (sizeof(T) == 2) {
-    if (p.Lk >= kLongKeys) {
-      if constexpr (DH == 128) {
+    const bool is_long = p.Lk >= kLongKeys;
+    if constexpr (DH == 128) {
+      if (is_long || prefer_g2(p, ncu)) {
         if (q_scaled) launch_g2<true>(p, stream, ncu);
         else launch_g2<false>(p, stream, ncu);
-      } else {
-        launch_w<T, DH, 8>(p, q_scaled, stream, ncu);
+        return;
       }
-      return;
+    } else {
+      if (is_long) {
+        launch_w<T, DH, 8>(p, q_scaled, stream, ncu);
+        return;
+      }
     }
+    launch_w<T, DH, 4>(p, q_scaled, stream, ncu);
+    return;
   }
-  launch_w<T, DH, 4>(p, q_scaled, stream, ncu);
+  // float32: its matrix rate, not the tile loads, bounds a wave (a
+  // 64-key tile of 32 queries is 7.8 us of MFMAs at head_dim 128), so what
+  // counts is the work spread over the CUs; 1170 tokens, 9 heads 164 -> 96 us,
+  // 3000 tokens, 12 heads 789 -> 664 against four query groups of 64-key tiles.
+  // (bf16 loses what it gains: its 32-key tiles are shorter than the loads'
+  // latency when the keys are not in the L2, as in a block.)
+  if constexpr (sizeof(T) == 4) launch_groups<T, DH>(p, q_scaled, stream);
 }
 
 size_t attention_split_bytes(int head_dim) {

@@ -1,0 +1,66 @@
+"""Attention over the sizes where its choice of kernel and its key groups can go
+wrong: fewer keys than a group's first tile, one more, ranges that leave the
+second key group nothing or one key, query counts around a workgroup's; and the
+two-group kernel below its long-key threshold, whole and with its last round
+split.  Reference: the oracle's two-pass softmax in float64.
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2607_06631_amd import binding as B
+from tests.gpu_util import rel_err, say, to_np
+from workloads.synth import bf16_round
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(dtype, dh, H, Lq, Lk, Bn, heads, qscale, split=False):
+    import torch
+    g = np.random.default_rng(Lq * 131 + Lk)
+    bf = dtype == "bf16"
+    tdt = torch.bfloat16 if bf else torch.float32
+    W = H * dh
+
+    def rand(shape, scale=1.0):
+        a = g.standard_normal(shape, dtype=np.float32) * np.float32(scale)
+        return bf16_round(a) if bf else a
+
+    q, k, v = rand((Bn, Lq, W), qscale), rand((Bn, Lk, W)), rand((Bn, Lk, W))
+    ldvt = -(-Lk // 64) * 64 + 64       # padded, garbage in the pad
+    vt = np.full((Bn, W, ldvt), np.nan, np.float32)
+    vt[:, :, :Lk] = v.transpose(0, 2, 1)
+    Q, K, Vt = (torch.from_numpy(a).cuda().to(tdt) for a in (q, k, vt))
+    Ot = torch.full((Bn, Lq + 1, W), float("nan"), device="cuda", dtype=tdt)
+    out = Ot.view(-1, W)[:Bn * Lq]
+    ws = None
+    if split:
+        ws = torch.empty(B.dif_attention_split_bytes(dh), dtype=torch.uint8, device="cuda")
+    B.dif_attention_ex(Q, K, Vt, out, Bn, Lq, Lk, H, dh, W, W, ldvt, W, 0, ws)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(Ot.view(-1, W)[Bn * Lq:]).all())
+    got = to_np(out).reshape(Bn, Lq, W)
+    errs = []
+    for h in heads:
+        c = slice(h * dh, (h + 1) * dh)
+        ref = np.stack([O.attention(q[b][:, c].astype(np.float64), k[b][:, c].astype(np.float64),
+                                    v[b][:, c].astype(np.float64), 1, dh) for b in range(Bn)])
+        errs.append(rel_err(got[:, :, c], ref))
+    return max(errs)
+
+
+@pytest.mark.parametrize("dtype,dh", [("bf16", 128), ("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("Lq,Lk", [(1, 1), (31, 31), (32, 32), (33, 33), (64, 63), (65, 64), (66, 65),
+                                   (127, 96), (128, 97), (129, 128), (63, 129), (200, 511)])
+def test_key_groups(dtype, dh, Lq, Lk):
+    say(f"attention groups {dtype} dh={dh} Lq={Lq} Lk={Lk}")
+    err = _case(dtype, dh, 3, Lq, Lk, 2, range(3), 3.0)
+    assert err <= (2e-2 if dtype == "bf16" else 1e-5)
+
+
+@pytest.mark.parametrize("H,Lq,Lk,split", [(42, 1290, 2049, False), (42, 1290, 2049, True),
+                                           (29, 2600, 2100, False), (29, 2600, 2100, True),
+                                           (30, 256, 1024, False), (12, 1000, 4095, True)])
+def test_below_the_long_key_threshold(H, Lq, Lk, split):
+    say(f"attention bf16 H={H} Lq={Lq} Lk={Lk} split={split}")
+    assert _case("bf16", 128, H, Lq, Lk, 1, (0, H - 1), 3.0, split) <= 2e-2
