@@ -652,33 +652,60 @@ hipError_t launch_ffn_norms(const T* w1, const float* b1, const T* w2, int D, in
 // ---------------------------------------------------------------------------
 // timestep embedding pieces
 // ---------------------------------------------------------------------------
-template <typename T>
+// HBM-bound (W is read once).  A wave takes R rows together, so a lane's slice
+// of x, twice W's bytes, is read once for them.  R = 4 where that leaves four
+// waves per SIMD ([30720, 5120] bf16: 57 us against 60 with one row), else 1 (of
+// 5120 rows 4 would leave one wave per SIMD: 20 us against 11).
+template <typename T, int GEMV_R>
 __global__ __launch_bounds__(R_THREADS) void gemv_kernel(const T* __restrict__ W,
                                                          const float* __restrict__ x,
                                                          const float* __restrict__ bias,
                                                          float* __restrict__ out, int N, int K) {
   constexpr int VEC = Chunk<T>::VEC;
-  const int n = blockIdx.x * R_WAVES + (threadIdx.x >> 6);
+  const int n0 = (blockIdx.x * R_WAVES + (threadIdx.x >> 6)) * GEMV_R;
   const int lane = threadIdx.x & 63;
-  if (n >= N) return;
-  const T* wr = W + (int64_t)n * K;
-  float acc = 0.f;
-  for (int k = lane * VEC; k < K; k += kWave * VEC) {
-    float w[VEC];
-    Chunk<T>::unpack(*reinterpret_cast<const u32x4*>(wr + k), w);
+  if (n0 >= N) return;
+  const T* wr[GEMV_R];
+  float acc[GEMV_R];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) acc += w[e] * x[k + e];
+  for (int r = 0; r < GEMV_R; ++r) {
+    wr[r] = W + (int64_t)min(n0 + r, N - 1) * K;
+    acc[r] = 0.f;
   }
-  acc = wave_sum(acc);
-  if (lane == 0) out[n] = acc + (bias ? bias[n] : 0.f);
+#pragma unroll 4
+  for (int k = lane * VEC; k < K; k += kWave * VEC) {
+    u32x4 raw[GEMV_R];
+#pragma unroll
+    for (int r = 0; r < GEMV_R; ++r) raw[r] = *reinterpret_cast<const u32x4*>(wr[r] + k);
+    float xv[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) xv[e] = x[k + e];
+#pragma unroll
+    for (int r = 0; r < GEMV_R; ++r) {
+      float w[VEC];
+      Chunk<T>::unpack(raw[r], w);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) acc[r] += w[e] * xv[e];
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < GEMV_R; ++r) {
+    acc[r] = wave_sum(acc[r]);
+    if (lane == 0 && n0 + r < N) out[n0 + r] = acc[r] + (bias ? bias[n0 + r] : 0.f);
+  }
 }
 
 template <typename T>
 hipError_t launch_gemv(const T* W, const float* x, const float* bias, float* out, int N, int K,
                        hipStream_t stream) {
   if (N <= 0) return hipSuccess;
-  hipLaunchKernelGGL((gemv_kernel<T>), dim3((N + R_WAVES - 1) / R_WAVES), dim3(R_THREADS), 0, stream,
-                     W, x, bias, out, N, K);
+  auto launch = [&](auto r_tag) {
+    constexpr int R = decltype(r_tag)::value, rows = R_WAVES * R;
+    hipLaunchKernelGGL((gemv_kernel<T, R>), dim3((N + rows - 1) / rows), dim3(R_THREADS), 0, stream, W, x,
+                       bias, out, N, K);
+  };
+  if (N >= 16384) launch(std::integral_constant<int, 4>{});
+  else launch(std::integral_constant<int, 1>{});
   return hipGetLastError();
 }
 
