@@ -22,7 +22,7 @@
 //            channels are dropped from the output width.
 //   GA_KCH   16-byte K chunk c of every B row is read from chunk kch[c] of
 //            that row (-1: zeros).  Used where dropped heads or FFN chunks
-//            shorten the reduction.  This kernel stages the chunk table in LDS once.
+//            shorten the reduction.
 // Masked rows / chunks get an offset past the descriptor's range, which the
 // buffer load returns as zero.
 #include <type_traits>
@@ -36,13 +36,11 @@ constexpr int BN_MAX = 256; // widest workgroup tile
 // 256 x 256 workgroup tile as 8 waves (2 x 4) of 128 x 64: each wave owns
 // TM x TN 32x32 output blocks; two LDS stages of BKC 16-byte chunks per operand
 // row.
-template <typename OutT, int EPI, int GA>
+template <typename OutT, int EPI>
 __global__ __launch_bounds__(512, 1) void gemm_nt_kernel(GemmParams<bf16, OutT> p) {
   using T = bf16;
-  static_assert(GA == GA_NONE || GA == GA_KCH, "row-gathered B runs gemm_ring.h");
   constexpr int WGM = 2, WGN = 4, TM = 4, TN = 2, BKC = G_BKC;
   constexpr int NW = WGM * WGN;
-  constexpr int NT = 64 * NW;
   constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32;
   constexpr int VEC = Chunk<T>::VEC;
   constexpr int BK = BKC * VEC;
@@ -58,7 +56,6 @@ __global__ __launch_bounds__(512, 1) void gemm_nt_kernel(GemmParams<bf16, OutT> 
   static_assert(LA * RPI * NLW == BM && LB * RPI * NLW == BN, "staging split");
   __shared__ u32x4 smem[2][BM + BN][BKC];
   static_assert(sizeof(smem) >= (size_t)NW * 64 * 64 * sizeof(float), "epilogue staging");
-  extern __shared__ uint32_t kch_lds[];   // GA_KCH: byte offset of each K chunk
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
@@ -110,22 +107,8 @@ __global__ __launch_bounds__(512, 1) void gemm_nt_kernel(GemmParams<bf16, OutT> 
   auto drow = [&](int i) { return (i * NLW + lw) * RPI + lane / BKC; };
   const int dchunk = swz<BKC>(drow(0), lane % BKC);
   a_off = (uint32_t)((drow(0) * p.lda + dchunk * VEC) * (int64_t)sizeof(T));
-  b_off = (uint32_t)((drow(0) * p.ldb + (GA == GA_KCH ? 0 : dchunk * VEC)) * (int64_t)sizeof(T));
+  b_off = (uint32_t)((drow(0) * p.ldb + dchunk * VEC) * (int64_t)sizeof(T));
   const int nk = p.K / BK;
-  if constexpr (GA == GA_KCH) {
-    for (int c = tid; c < p.K / VEC; c += NT) {
-      const int u = p.kch[c];
-      kch_lds[c] = u >= 0 ? (uint32_t)u * 16u : kMasked;
-    }
-    __syncthreads();
-  }
-
-  uint32_t kb = 0;   // GA_KCH: byte offset of this lane's chunk in the next tile to issue
-  auto kb_fetch = [&](int kt) {
-    if constexpr (GA == GA_KCH) {
-      if (kt < nk) kb = kch_lds[kt * BKC + dchunk];
-    }
-  };
   typedef __attribute__((address_space(3))) void lds_t;
   // load u (0 .. LPT-1) of this loading wave's share of tile kt into stage
   // st: A rows, then B rows (LDS destinations from a scalar wave index)
@@ -144,10 +127,7 @@ __global__ __launch_bounds__(512, 1) void gemm_nt_kernel(GemmParams<bf16, OutT> 
     } else {
       const int i = u - LA;
       lds_t* dst = (lds_t*)&smem[st][BM + (i * NLW + lw_s) * RPI][0];
-      if constexpr (GA == GA_KCH)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, b0 + i * b_step + kb, 0, 0, 0);
-      else
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, b0 + i * b_step, koff, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, b0 + i * b_step, koff, 0, 0);
     }
 #endif
   };
@@ -186,11 +166,7 @@ __global__ __launch_bounds__(512, 1) void gemm_nt_kernel(GemmParams<bf16, OutT> 
   // stage), compute tile kt while requesting tile kt+1 into that stage.  Half
   // of the loads go out before the first k-step and half after its MFMAs:
   // issued in one burst, or spread over the k-steps, they measured slower.
-  if (nk > 0) {
-    kb_fetch(0);
-    issue(0);
-    kb_fetch(1);
-  }
+  if (nk > 0) issue(0);
   auto ktile = [&](int kt, auto st_c) {
     constexpr int st = decltype(st_c)::value;
     using NS = std::integral_constant<int, st ^ 1>;
@@ -239,7 +215,6 @@ __global__ __launch_bounds__(512, 1) void gemm_nt_kernel(GemmParams<bf16, OutT> 
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    kb_fetch(kt + 2);
   };
   {
     int kt = 0;
@@ -432,20 +407,19 @@ __global__ __launch_bounds__(512, 1) void gemm_nt_kernel(GemmParams<bf16, OutT> 
   }
 }
 
-// LDS left beside the two operand stages (2 x 512 rows x 128 B) for the
-// K-chunk table
-constexpr int kMaxKChunks = (160 * 1024 - 2 * 512 * G_BKC * 16) / 4;
+// The longest K-chunk table of a gathered B (a 16-bit entry per chunk beside the
+// operand tiles in LDS)
+constexpr int kMaxKChunks = 8192;
 
-// The tile by pick_tile: 256 x 256 here (bf16 only, and not for row-gathered
-// B), any other shape in gemm_ring.h.
+// The tile by pick_tile: 256 x 256 here for plain bf16 operands, all else in
+// gemm_ring.h.
 template <typename T, typename OutT, int EPI, int GA>
 hipError_t launch_tile(const GemmParams<T, OutT>& p, hipStream_t stream) {
   const int shape = pick_tile<T>(p.M, p.N, p.nseg, p.K);
-  if constexpr (sizeof(T) == 2 && GA != GA_ROWS) {
+  if constexpr (sizeof(T) == 2 && GA == GA_NONE) {
     if (shape == TS_256) {
       const int tiles = ((p.M + 255) / 256) * ((p.N + 255) / 256) * p.nseg;
-      const size_t dyn = GA == GA_KCH ? (size_t)(p.K / Chunk<T>::VEC) * sizeof(uint32_t) : 0;
-      hipLaunchKernelGGL((gemm_nt_kernel<OutT, EPI, GA>), dim3(tiles), dim3(512), dyn, stream, p);
+      hipLaunchKernelGGL((gemm_nt_kernel<OutT, EPI>), dim3(tiles), dim3(512), 0, stream, p);
       return hipGetLastError();
     }
   }

@@ -58,6 +58,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_ring_kernel(GemmPara
     else if constexpr (st == 4) return s4_;
     else return s5_;
   };
+  extern __shared__ uint16_t kch_lds[];   // GA_KCH: source chunk of each K chunk
+
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
   const int g = lane >> 4, col = lane & 15;
@@ -94,71 +96,65 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_ring_kernel(GemmPara
     const int q = i * NW + wave_s;
     return (i + 1) * NW <= G8 || q < G8 ? q : q - NW;
   };
+  // lane offsets without the k offset: row * ld + chunk of load instruction 0,
+  // plus i times NW * 8 rows (A's; B's start BM rows in, modulo 2^32); gathered
+  // B rows need an offset per instruction
   const uint32_t a_ld = (uint32_t)(p.lda * ES), b_ld = (uint32_t)(p.ldb * ES);
-  // lane offsets inside group i: row * ld + chunk, without the k offset
-  uint32_t off[LPT];
+  const uint32_t lr0 = (uint32_t)(wave * 8 + lrow);
+  const uint32_t a_off = lr0 * a_ld + dchunk * 16;
+  const uint32_t b_off = (lr0 - BM) * b_ld + (GA == GA_KCH ? 0 : dchunk * 16);
+  uint32_t r_off[GA == GA_ROWS ? LPT : 1];
+  if constexpr (GA == GA_ROWS) {
 #pragma unroll
-  for (int i = 0; i < LPT; ++i) {
-    const int q = group(i);
-    const uint32_t ra = (uint32_t)(q * 8 + lrow), rb = (uint32_t)(q * 8 + lrow - BM);
-    uint32_t ob;
-    if constexpr (GA == GA_ROWS) {
-      const int n = n0 + (int)rb;
+    for (int i = 0; i < LPT; ++i) {
+      const int q = group(i), n = n0 + q * 8 + lrow - BM;
       const int r = q >= GA8 && n < p.N ? p.rows[n] : -1;
-      ob = r >= 0 ? (uint32_t)((r * p.ldb + dchunk * VEC) * ES) : kMasked;
-    } else if constexpr (GA == GA_KCH) {
-      ob = rb * b_ld;
-    } else {
-      ob = rb * b_ld + dchunk * 16;
+      r_off[i] = r >= 0 ? (uint32_t)((r * p.ldb + dchunk * VEC) * ES) : kMasked;
     }
-    off[i] = q < GA8 ? ra * a_ld + dchunk * 16 : ob;
   }
   const int nk = p.K / BK;
+  if constexpr (GA == GA_KCH) {   // (the host keeps chunk numbers below 65535)
+    for (int c = tid; c < p.K / VEC; c += 64 * NW) kch_lds[c] = (uint16_t)p.kch[c];
+    __syncthreads();
+  }
   // load instruction i of tile kt into its slot
-  // GA_KCH: byte offset of this lane's chunk of a tile.  The tile's eight table
-  // entries come by a scalar load (uniform address; waited for by the count
-  // that the fragment reads use), the lane picks its own.
-  typedef int32_t i32x8 __attribute__((ext_vector_type(8), aligned(4)));
-  uint32_t kb = 0;
-  i32x8 ke;
+  // GA_KCH: byte offset of this lane's chunk of a tile, from the chunk table in
+  // LDS (16-bit entries, so that three 160 x 256 slots leave room for it).  Read
+  // half a tile ahead, in order with the fragment reads.  (A scalar load of the
+  // tile's eight entries makes every wait for a fragment wait for it as well:
+  // 13608 x 5120 x 2432 took 407 us on 256 x 256 tiles, 328 with the table.)
+  uint32_t kb = 0, ke = 0;
   auto kb_load = [&](int kt) __attribute__((always_inline)) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    if constexpr (GA == GA_KCH) {
-      typedef __attribute__((address_space(4))) const i32x8 const_i32x8;
-      ke = *(const_i32x8*)(uintptr_t)(p.kch + kt * G_BKC);
-    }
-#endif
+    if constexpr (GA == GA_KCH) ke = kch_lds[kt * G_BKC + dchunk];
   };
   auto kb_pick = [&]() __attribute__((always_inline)) {
-    if constexpr (GA == GA_KCH) {
-#if defined(__HIP_DEVICE_COMPILE__)
-      asm volatile("" : "+s"(ke));   // (the eight values, not a load per lane)
-#endif
-      const int b0 = dchunk & 1, b1 = dchunk & 2, b2 = dchunk & 4;
-      const int x0 = b0 ? ke[1] : ke[0], x1 = b0 ? ke[3] : ke[2], x2 = b0 ? ke[5] : ke[4],
-                x3 = b0 ? ke[7] : ke[6];
-      const int y0 = b1 ? x1 : x0, y1 = b1 ? x3 : x2;
-      const int u = b2 ? y1 : y0;
-      kb = u >= 0 ? (uint32_t)u * 16u : kMasked;
-    }
+    if constexpr (GA == GA_KCH) kb = ke != 0xffffu ? ke * 16u : kMasked;
   };
   auto issue_one = [&](int kt, auto st_c, int i) __attribute__((always_inline)) {
 #if defined(__HIP_DEVICE_COMPILE__)
     typedef __attribute__((address_space(3))) void lds_t;
     const int koff = kt * BK * (int)ES;
     const int q = group(i);
+    const uint32_t at = (uint32_t)(q & ~(NW - 1)) * 8;   // rows of instruction i past the first's
     lds_t* dst = (lds_t*)&slot(st_c)[q * 8][0];
+    // (opaque copies: the offsets are formed here, not kept per instruction)
+    uint32_t a0 = a_off, b0 = b_off;
+    asm volatile("" : "+v"(a0), "+v"(b0));
+    const uint32_t oa = a0 + at * a_ld;
+    uint32_t ob;
+    if constexpr (GA == GA_ROWS) ob = r_off[i];
+    else ob = b0 + at * b_ld + kb;
+    constexpr bool KOFF = GA != GA_KCH;   // (a gathered chunk's offset is in kb)
     if ((i + 1) * NW <= GA8) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, dst, 16, off[i], koff, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, dst, 16, oa, koff, 0, 0);
     } else if (i * NW >= GA8) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, off[i] + kb, GA == GA_KCH ? 0 : koff, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, ob, KOFF ? koff : 0, 0, 0);
     } else {   // some waves' groups are A's, the others' B's
       const bool is_a = q < GA8;
       const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
           const_cast<T*>(is_a ? p.A + (int64_t)m0 * p.lda : b_base), (short)0, is_a ? a_bytes : b_bytes,
           kRsrcWord3);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, off[i] + (is_a ? 0u : kb),
-                                               GA == GA_KCH && !is_a ? 0 : koff, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, is_a ? oa : ob, is_a || KOFF ? koff : 0, 0, 0);
     }
 #endif
   };
@@ -439,24 +435,27 @@ constexpr int kCus = 256;
 // on each CU; cn: the same divided among several per CU; f: fixed cost of a
 // round of tiles (prologue, first loads, epilogue); occ: workgroups a CU
 // holds.  Measured on 128 .. 1024 tiles at K = 1024 and 4096 (bf16), 512 and
-// 2048 (float32).
+// 2048 (float32).  g: what a k-tile costs more in several rounds of a long
+// reduction, where workgroups drift apart and share less of the L2 (bf16,
+// 6000-24000 rows at K = 5120-12736; nothing at K = 1536).
 struct TileShape {
   int bm, bn, occ;
-  float c1, cn, f;
+  float c1, cn, f, g;
 };
 enum { TS_256 = 0, TS_224, TS_192, TS_160, TS_128W, TS_96W, TS_128, TS_96, TS_64, TS_64S, TS_32, TS_COUNT };
 template <typename T>
 inline const TileShape* tile_shapes() {
   static constexpr TileShape bf[TS_COUNT] = {
-      {256, 256, 1, 1.38f, 1.38f, 13.f}, {224, 256, 1, 1.23f, 1.23f, 11.f}, {192, 256, 1, 1.075f, 1.075f, 10.f},
-      {160, 256, 1, 0.91f, 0.91f, 9.f},  {128, 256, 1, 0.74f, 0.74f, 8.f},  {96, 256, 1, 0.605f, 0.605f, 7.f},
-      {128, 128, 1, 0.475f, 0.475f, 7.5f}, {96, 128, 1, 0.36f, 0.36f, 6.f}, {64, 128, 2, 0.31f, 0.31f, 5.f},
-      {64, 64, 2, 0.165f, 0.165f, 4.5f}, {32, 32, 3, 0.075f, 0.07f, 5.f}};
+      {256, 256, 1, 1.38f, 1.38f, 13.f, .10f},   {224, 256, 1, 1.23f, 1.23f, 11.f, .18f},
+      {192, 256, 1, 1.075f, 1.075f, 10.f, .15f}, {160, 256, 1, 0.91f, 0.91f, 9.f, .13f},
+      {128, 256, 1, 0.74f, 0.74f, 8.f, .21f},    {96, 256, 1, 0.605f, 0.605f, 7.f, .27f},
+      {128, 128, 1, 0.475f, 0.475f, 7.5f, .25f}, {96, 128, 1, 0.36f, 0.36f, 6.f, .25f},
+      {64, 128, 2, 0.31f, 0.31f, 5.f, .25f},     {64, 64, 2, 0.165f, 0.165f, 4.5f, .25f},
+      {32, 32, 3, 0.075f, 0.07f, 5.f, .25f}};
   // (the wide tiles gain float32 nothing: the matrix rate bounds it)
   static constexpr TileShape f32[TS_COUNT] = {
-      {0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0},
-      {0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0}, {96, 128, 2, 1.33f, 1.30f, 6.f}, {64, 128, 2, 0.90f, 0.86f, 6.f},
-      {64, 64, 2, 0.457f, 0.44f, 4.5f}, {32, 32, 3, 0.132f, 0.117f, 4.2f}};
+      {}, {}, {}, {}, {}, {}, {}, {96, 128, 2, 1.33f, 1.30f, 6.f, 0.f}, {64, 128, 2, 0.90f, 0.86f, 6.f, 0.f},
+      {64, 64, 2, 0.457f, 0.44f, 4.5f, 0.f}, {32, 32, 3, 0.132f, 0.117f, 4.2f, 0.f}};
   return sizeof(T) == 2 ? bf : f32;
 }
 
@@ -479,10 +478,14 @@ inline int pick_tile(int M, int N, int nseg, int K) {
     const int64_t n = (tiles + kCus - 1) / kCus;
     const float fill = (float)tiles / (float)(n * kCus);
     const float rounds = (float)((n + t.occ - 1) / t.occ);
-    const float est = nk * (n == 1 ? t.c1 : (float)n * t.cn) * (0.6f + 0.4f * fill) +
+    const float longk = n == 1 ? 0.f : nk <= 24.f ? 0.f : nk >= 80.f ? 1.f : (nk - 24.f) / 56.f;
+    const float est = nk * (n == 1 ? t.c1 : (float)n * t.cn) * (0.6f + 0.4f * fill) * (1.f + longk * t.g) +
                       t.f * (0.5f + 0.5f * rounds);
-    if (tbest == 0.f || est < tbest) {
-      tbest = est;
+    // (256 x 256 unless another is 2 % better: the estimate's error.  15759 x
+    // 4601 x 5504, 0.7 % better on 160 x 256, took 661 us against 643.)
+    const float bias = i == TS_256 ? 0.98f : 1.f;
+    if (tbest == 0.f || est * bias < tbest) {
+      tbest = est * bias;
       best = i;
     }
   }
@@ -493,17 +496,21 @@ template <typename T, typename OutT, int EPI, int GA, int WGM, int WGN, int AM, 
 void launch_ring_cfg(const GemmParams<T, OutT>& p, hipStream_t stream) {
   constexpr int BM = WGM * AM * 16, BN = WGN * AN * 16;
   const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN) * p.nseg;
+  const size_t dyn = GA == GA_KCH ? (size_t)(p.K / Chunk<T>::VEC) * sizeof(uint16_t) : 0;
   hipLaunchKernelGGL((gemm_ring_kernel<T, OutT, EPI, GA, WGM, WGN, AM, AN, NST, OCC>), dim3(tiles),
-                     dim3(64 * WGM * WGN), 0, stream, p);
+                     dim3(64 * WGM * WGN), dyn, stream, p);
 }
 
 template <typename T, typename OutT, int EPI, int GA>
 hipError_t launch_ring_shape(int shape, const GemmParams<T, OutT>& p, hipStream_t s) {
   if constexpr (sizeof(T) == 2) {
+    // (three 160 x 256 slots leave 4 KB for the chunk table; 128 x 256, 16 KB,
+    // fits the longest)
+    if (GA == GA_KCH && shape == TS_160 && p.K / Chunk<T>::VEC > 2048) shape = TS_128W;
     switch (shape) {
       case TS_256:
-        // row-gathered B; the other modes' largest problems run gemm.hip
-        if constexpr (GA == GA_ROWS) launch_ring_cfg<T, OutT, EPI, GA, 2, 4, 8, 4, 2, 1>(p, s);
+        // gathered B; the largest plain problems run gemm.hip
+        if constexpr (GA != GA_NONE) launch_ring_cfg<T, OutT, EPI, GA, 2, 4, 8, 4, 2, 1>(p, s);
         else return hipErrorInvalidValue;
         break;
       case TS_224: launch_ring_cfg<T, OutT, EPI, GA, 2, 4, 7, 4, 2, 1>(p, s); break;
