@@ -137,9 +137,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_ring_kernel(GemmPara
     const int q = group(i);
     const uint32_t at = (uint32_t)(q & ~(NW - 1)) * 8;   // rows of instruction i past the first's
     lds_t* dst = (lds_t*)&slot(st_c)[q * 8][0];
-    // (opaque copies: the offsets are formed here, not kept per instruction)
     uint32_t a0 = a_off, b0 = b_off;
-    asm volatile("" : "+v"(a0), "+v"(b0));
+    // (opaque copies: formed here, not kept per instruction, for which the
+    // chunk table's values leave no registers on the 224-row tile)
+    if constexpr (GA == GA_KCH) asm volatile("" : "+v"(a0), "+v"(b0));
     const uint32_t oa = a0 + at * a_ld;
     uint32_t ob;
     if constexpr (GA == GA_ROWS) ob = r_off[i];
