@@ -384,7 +384,7 @@ __global__ __launch_bounds__(64 * NQ * NK, 8 / (NQ * NK)) void flash_attn_kernel
       // O^T += V^T P^T, and this half's lane-partial row sum
       u32x4 pc[NPC];
       float lh = 0.f;
-      auto probs = [&]() __attribute__((always_inline)) {
+      auto probs = [&]() {
 #pragma unroll
         for (int u = 0; u < NPC; ++u) {
           float pv[VEC];
@@ -1255,8 +1255,8 @@ void launch_w(AttnParams<T> p, bool q_scaled, hipStream_t stream, int ncu) {
     hipLaunchKernelGGL((attn_merge_kernel<T, DH, BMQ>), dim3(nsplit, BMQ / MERGE_Q), dim3(256), 0, stream, p, nsplit);
 }
 
-// Two query groups and two key groups of 32-key tiles (no key split across
-// workgroups).
+// float32: two query groups and two key groups of 32-key tiles (no key split
+// across workgroups).
 template <typename T, int DH>
 void launch_groups(AttnParams<T> p, bool q_scaled, hipStream_t stream) {
   constexpr int NQ = 2, NK = 2, BN = 32;
@@ -1289,6 +1289,30 @@ bool prefer_g2(const AttnParams<T>& p, int ncu) {
   return 1.03f * (nt * 1.7f * rounds + (split ? 16.f : 8.f)) < nt * 2.27f * four;
 }
 
+// float32: whether the key groups are estimated faster than four query groups of
+// 64-key tiles.  The matrix rate bounds a wave (a 64-key tile of 32 queries takes
+// per64 us), so a workgroup of key groups takes half the time for half the
+// queries: it pays where the 128-query workgroups leave CUs idle (1170 tokens, 9
+// heads, head_dim 128: 164 -> 96 us) or a last round nearly empty (3000 tokens,
+// 12 heads: 789 -> 664), and costs its merge and a second set of tiles where they
+// do not (947 tokens, 64 heads: 271 -> 311) or where there is a tile or two of
+// keys (2216 x 8, 24 heads: 40 -> 60).
+template <typename T, int DH>
+bool prefer_groups(const AttnParams<T>& p, int ncu) {
+  constexpr int kChip = 256, occ = DH == 128 ? 1 : 2;
+  constexpr float per64 = DH == 128 ? 9.f : 4.2f, fixed4 = 8.f, fixed2 = DH == 128 ? 12.f : 10.f;
+  auto up = [](int64_t n, int64_t m) { return (float)((n + m - 1) / m); };
+  const int64_t bh = (int64_t)p.B * p.H, items4 = (p.Lq + 127) / 128 * bh, items2 = (p.Lq + 63) / 64 * bh;
+  const int rem = ncu > 0 ? (int)(items4 % (2 * ncu)) : 0;   // (as launch_w splits)
+  const bool split = p.part && rem > 0 && rem <= ncu && rem <= kMaxSplitItems && p.Lk / AT_BN >= 4;
+  const float full = up(items4 - (split ? rem : 0), kChip), half = split ? up(2 * rem, kChip) : 0.f;
+  const float t4 = (full + 0.5f * half) * up(p.Lk, 64) * per64 +
+                   fixed4 * up((int64_t)(full + half), occ) + (split ? 8.f : 0.f);
+  const float n2 = up(items2, kChip);
+  const float t2 = n2 * up((p.Lk + 31) / 32, 2) * 0.5f * per64 + fixed2 * up((int64_t)n2, occ);
+  return t2 < t4;
+}
+
 template <typename T, int DH>
 void launch_dh(const AttnParams<T>& p, bool q_scaled, hipStream_t stream, int ncu) {
   if constexpr (sizeof(T) == 2) {
@@ -1305,16 +1329,15 @@ void launch_dh(const AttnParams<T>& p, bool q_scaled, hipStream_t stream, int nc
         return;
       }
     }
-    launch_w<T, DH, 4>(p, q_scaled, stream, ncu);
-    return;
+  } else {
+    // (bf16 in key groups loses what it gains: its 32-key tiles are shorter than
+    // the loads' latency when the keys are not in the L2, as in a block)
+    if (prefer_groups<T, DH>(p, ncu)) {
+      launch_groups<T, DH>(p, q_scaled, stream);
+      return;
+    }
   }
-  // float32: its matrix rate, not the tile loads, bounds a wave (a
-  // 64-key tile of 32 queries is 7.8 us of MFMAs at head_dim 128), so what
-  // counts is the work spread over the CUs; 1170 tokens, 9 heads 164 -> 96 us,
-  // 3000 tokens, 12 heads 789 -> 664 against four query groups of 64-key tiles.
-  // (bf16 loses what it gains: its 32-key tiles are shorter than the loads'
-  // latency when the keys are not in the L2, as in a block.)
-  if constexpr (sizeof(T) == 4) launch_groups<T, DH>(p, q_scaled, stream);
+  launch_w<T, DH, 4>(p, q_scaled, stream, ncu);
 }
 
 size_t attention_split_bytes(int head_dim) {
