@@ -482,9 +482,13 @@ inline int pick_tile(int M, int N, int nseg, int K) {
     const float longk = n == 1 ? 0.f : nk <= 24.f ? 0.f : nk >= 80.f ? 1.f : (nk - 24.f) / 56.f;
     const float est = nk * (n == 1 ? t.c1 : (float)n * t.cn) * (0.6f + 0.4f * fill) * (1.f + longk * t.g) +
                       t.f * (0.5f + 0.5f * rounds);
-    // (256 x 256 unless another is 2 % better: the estimate's error.  15759 x
-    // 4601 x 5504, 0.7 % better on 160 x 256, took 661 us against 643.)
-    const float bias = i == TS_256 ? 0.98f : 1.f;
+    // 256 x 256 unless another shape is better by more than the estimate errs: 2 %
+    // per round, up to 8 % (under a long load the clock falls with the LDS reads
+    // per flop: 13911 x 7076 x 1600, seven rounds, estimated 8 % better on 224 x
+    // 256, took 347 us against 313), and 8 % for less than eight k-tiles, whose
+    // rounds do not overlap (15747 x 988 x 64: 15.8 us on 128 x 256 against 14.2).
+    const float margin = nk < 8.f ? 0.08f : 0.02f * (n < 4 ? (float)n : 4.f);
+    const float bias = i == TS_256 ? 1.f - margin : 1.f;
     if (tbest == 0.f || est * bias < tbest) {
       tbest = est * bias;
       best = i;
