@@ -234,6 +234,16 @@ constexpr int QK_WAVES = 8;    // 16 KB of loads in flight per wave; registers f
 // the registers of several spill.)
 template <int NSEG, int MAXC>
 constexpr int qk_rpw() { return NSEG == 2 ? 16 : MAXC > 12 ? 1 : 4; }
+// A rotated pair is (x0 cos - x1 sin, x0 sin + x1 cos), each with one product
+// rounded and the other inside a fused multiply-add, written out so that the
+// result does not hang on which product the compiler fuses (left to it, instances
+// of one width differed with their rows per wave and between builds).  The first
+// coordinate rounds x1 sin; the second rounds x0 sin in the instances named here
+// and x1 cos in the others, which is what each width has always returned.
+template <typename T, int MAXC, int NSEG>
+constexpr bool qk_rounds_x0() {
+  return MAXC == 16 || (MAXC == 12 && sizeof(T) == 2) || (MAXC == 8 && NSEG == 2);
+}
 template <typename T, int MAXC, int NSEG, int RPW>
 __global__ __launch_bounds__(64 * QK_WAVES) void qk_norm_kernel(T* buf, int64_t ld, int rows, int a,
                                                             int nseg, int off0, int off1,
@@ -363,8 +373,9 @@ __global__ __launch_bounds__(64 * QK_WAVES) void qk_norm_kernel(T* buf, int64_t 
 #pragma unroll
             for (int k = 0; k < NP; ++k) {
               const float x0 = out[2 * k], x1 = out[2 * k + 1];
-              out[2 * k] = x0 * cs[k] - x1 * sn[k];
-              out[2 * k + 1] = x0 * sn[k] + x1 * cs[k];
+              out[2 * k] = fmaf(x0, cs[k], -(x1 * sn[k]));
+              if constexpr (qk_rounds_x0<T, MAXC, NSEG>()) out[2 * k + 1] = fmaf(x1, cs[k], x0 * sn[k]);
+              else out[2 * k + 1] = fmaf(x0, sn[k], x1 * cs[k]);
             }
           }
           *reinterpret_cast<u32x4*>(xr + c * VEC) = Chunk<T>::pack(out);
