@@ -303,8 +303,9 @@ __global__ __launch_bounds__(64 * NQ * NK, 8 / (NQ * NK)) void flash_attn_kernel
   const float uscale = SC ? 1.f : p.c;   // MFMA output units -> log2 units
 
   // S^T of half kk of the tile in buffer buf, plus c0 (an accumulator
-  // initialiser); K fragments are read in batches of KB ahead of their MFMAs.
-  auto scores = [&](int buf, int kk, const f32x16& c0) __attribute__((always_inline)) {
+  // initialiser), in key group grp's tile; K fragments are read in batches of KB
+  // ahead of their MFMAs.
+  auto scores = [&](int grp, int buf, int kk, const f32x16& c0) __attribute__((always_inline)) {
     constexpr int KB = NQS >= 8 ? NQS / 2 : NQS;
     f32x16 s = c0;
     __builtin_amdgcn_sched_barrier(0);
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(64 * NQ * NK, 8 / (NQ * NK)) void flash_attn_kernel
     for (int s0 = 0; s0 < NQS; s0 += KB) {
       u32x4 kf[KB];
 #pragma unroll
-      for (int st = 0; st < KB; ++st) kf[st] = ks_[kg][buf][kk * 32 + col][swz<KCH>(col, 2 * (s0 + st) + g)];
+      for (int st = 0; st < KB; ++st) kf[st] = ks_[grp][buf][kk * 32 + col][swz<KCH>(col, 2 * (s0 + st) + g)];
 #pragma unroll
       for (int st = 0; st < KB; ++st) Mma<T>::step(s, kf[st], qf[s0 + st]);
     }
@@ -327,21 +328,24 @@ __global__ __launch_bounds__(64 * NQ * NK, 8 / (NQ * NK)) void flash_attn_kernel
       if (key + 16 * g + r >= p.Lk) s[r] = -INFINITY;
   };
 
-  const bool any = NK == 1 || t0 < t1;   // (a key group may have no keys)
-  if (any) load_tile(t0, 0);
+  if (NK == 1 || t0 < t1) load_tile(t0, 0);   // (a key group may have no keys)
   wait_vmcnt<0>();   // this wave's direct-to-LDS loads have landed
   __syncthreads();   // ... and every other wave's
 
   // Initial base: the max of each query's first 32 scores of the range (its
-  // first key exists, so it is finite).  negm holds -m in MFMA output units.
-  float m_run = -INFINITY;
+  // first key exists, so it is finite), with key groups those of the first
+  // group's for all, as one walk over the keys would have it: the first keys of
+  // a later group may all score -inf, and a base of -inf makes NaNs of them.
+  // negm holds -m in MFMA output units.
+  float m_run;
   f32x16 negm;
-  if (any) {
+  {
+    const int key0 = NK == 1 ? t0 * AT_BN : 0;
     f32x16 z;
 #pragma unroll
     for (int r = 0; r < 16; ++r) z[r] = 0.f;
-    f32x16 s0 = scores(0, 0, z);
-    if (t0 * AT_BN + 32 > p.Lk) mask(s0, t0 * AT_BN);
+    f32x16 s0 = scores(0, 0, 0, z);
+    if (key0 + 32 > p.Lk) mask(s0, key0);
     float mx = -INFINITY;
 #pragma unroll
     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s0[r]);
@@ -364,7 +368,7 @@ __global__ __launch_bounds__(64 * NQ * NK, 8 / (NQ * NK)) void flash_attn_kernel
 #pragma unroll
     for (int kk = 0; kk < BN / 32; ++kk) {
       __builtin_amdgcn_sched_barrier(0);   // halves are not interleaved (register budget)
-      f32x16 s = scores(buf, kk, negm);   // (scores - m) in MFMA output units
+      f32x16 s = scores(kg, buf, kk, negm);   // (scores - m) in MFMA output units
       // (the tail tile masks before its V^T reads: fewer registers live
       // across the branch)
       if (MASKED && key0 + kk * 32 + 32 > p.Lk) mask(s, key0 + kk * 32);
@@ -522,7 +526,7 @@ __global__ __launch_bounds__(64 * NQ * NK, 8 / (NQ * NK)) void flash_attn_kernel
         mk[k] = reinterpret_cast<const float*>(slot(k) + SLOT)[lane];
         mx = fmaxf(mx, mk[k]);
       }
-      // (group 0 has keys, so mx is finite; an empty group's 2^-inf is zero)
+      // (every group starts from the first one's base, so all are finite)
 #pragma unroll
       for (int k = 0; k < NK; ++k) a[k] = __builtin_amdgcn_exp2f(mk[k] - mx);
       l *= a[0];

@@ -64,3 +64,34 @@ def test_key_groups(dtype, dh, Lq, Lk):
 def test_below_the_long_key_threshold(H, Lq, Lk, split):
     say(f"attention bf16 H={H} Lq={Lq} Lk={Lk} split={split}")
     assert _case("bf16", 128, H, Lq, Lk, 1, (0, H - 1), 3.0, split) <= 2e-2
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("lo,hi,Lk", [(128, 160, 256), (96, 193, 193), (40, 256, 256), (64, 65, 65)])
+def test_keys_whose_scores_overflow_downwards(dh, lo, hi, Lk):
+    """Keys [lo, hi), which begin the second key group's range or are all of it,
+    score -inf for every query: they weigh nothing, and the result is the
+    attention over the others (1e25 * -1e25 overflows float32; the other keys
+    meet that channel of the queries with zero)."""
+    import torch
+    say(f"attention -inf scores dh={dh} keys {lo}..{hi} of {Lk}")
+    g = np.random.default_rng(lo + Lk)
+    H, Lq = 3, 130
+    W = H * dh
+    q, k, v = (g.standard_normal((n, W), dtype=np.float32) for n in (Lq, Lk, Lk))
+    q[:, ::dh], k[:, ::dh] = 1e25, 0
+    k[lo:hi, ::dh] = -1e25
+    ldvt = -(-Lk // 64) * 64
+    vt = np.zeros((W, ldvt), np.float32)
+    vt[:, :Lk] = v.T
+    Q, K, Vt = (torch.from_numpy(a).cuda() for a in (q, k, vt))
+    out = torch.empty_like(Q)
+    B.dif_attention_ex(Q, K, Vt, out, 1, Lq, Lk, H, dh, W, W, ldvt, W, 0, None)
+    torch.cuda.synchronize()
+    keep = np.r_[0:lo, hi:Lk]
+    q[:, ::dh] = 0
+    for h in range(H):
+        c = slice(h * dh, (h + 1) * dh)
+        ref = O.attention(q[:, c].astype(np.float64), k[keep][:, c].astype(np.float64),
+                          v[keep][:, c].astype(np.float64), 1, dh)
+        assert rel_err(to_np(out)[:, c], ref) <= 1e-5
