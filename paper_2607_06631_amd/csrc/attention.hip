@@ -1219,16 +1219,30 @@ __global__ __launch_bounds__(256, 1) void flash_attn_g2_kernel(AttnParams<bf16> 
   }
 }
 
+// Workgroups of bmq queries each, and how many of them are split along the keys:
+// when the last round (of ncu CUs with per_cu workgroups each) would be at most
+// half full, its items become two workgroups of half the keys each, so the round
+// is full and half as long; a merge pass combines the halves.  The launches and
+// the estimates that choose between them both ask here.
+struct KeySplit {
+  int items, nsplit;
+};
+template <typename T>
+KeySplit key_split(const AttnParams<T>& p, int bmq, int per_cu, int ncu) {
+  const int items = ((p.Lq + bmq - 1) / bmq) * p.H * p.B, slots = ncu * per_cu;
+  const int rem = slots > 0 ? items % slots : 0;
+  const bool split = p.part && rem > 0 && 2 * rem <= slots && rem <= kMaxSplitItems && p.Lk / AT_BN >= 4;
+  return {items, split ? rem : 0};
+}
+// CUs an estimate counts on (ncu 0: not given, the launch is not split)
+inline int est_cus(int ncu) { return ncu > 0 ? ncu : kCus; }
+
 template <bool SC>
 void launch_g2(AttnParams<bf16> p, hipStream_t stream, int ncu) {
   constexpr int BMQ = 256;
-  const int items = ((p.Lq + BMQ - 1) / BMQ) * p.H * p.B;
-  const int rem = ncu > 0 ? items % ncu : 0;
-  const int nfull = p.Lk / AT_BN;
-  int nsplit = 0;
-  if (p.part && rem > 0 && 2 * rem <= ncu && rem <= kMaxSplitItems && nfull >= 4) nsplit = rem;
+  const auto [items, nsplit] = key_split(p, BMQ, 1, ncu);
   p.nreg = items - nsplit;
-  p.split_tile = (nfull / 2) & ~1;
+  p.split_tile = (p.Lk / AT_BN / 2) & ~1;
   hipLaunchKernelGGL((flash_attn_g2_kernel<SC>), dim3(p.nreg + 2 * nsplit), dim3(256), 0, stream, p);
   if (nsplit > 0)
     hipLaunchKernelGGL((attn_merge_kernel<bf16, 128, BMQ>), dim3(nsplit, BMQ / MERGE_Q), dim3(256), 0, stream, p, nsplit);
@@ -1237,19 +1251,10 @@ void launch_g2(AttnParams<bf16> p, hipStream_t stream, int ncu) {
 template <typename T, int DH, int W>
 void launch_w(AttnParams<T> p, bool q_scaled, hipStream_t stream, int ncu) {
   constexpr int BMQ = W * 32;
-  const int items = ((p.Lq + BMQ - 1) / BMQ) * p.H * p.B;
-  // Workgroups fill a CU (W = 8) or half of one (W = 4).  When the last
-  // round of workgroups would be at most half full, its items are split
-  // along the keys into two halves each, so the round is full and half as
-  // long; a merge pass combines the halves.
-  const int slots = ncu * (W == 8 ? 1 : 2);
-  const int rem = slots > 0 ? items % slots : 0;
-  const int nfull = p.Lk / AT_BN;
-  int nsplit = 0;
-  if (p.part && rem > 0 && 2 * rem <= slots && rem <= kMaxSplitItems && nfull >= 4 && BMQ <= 256)
-    nsplit = rem;
+  static_assert(BMQ <= 256, "a split item's queries fit the workspace region");
+  const auto [items, nsplit] = key_split(p, BMQ, W == 8 ? 1 : 2, ncu);   // (W = 4: two share a CU)
   p.nreg = items - nsplit;
-  p.split_tile = (nfull / 2) & ~1;
+  p.split_tile = (p.Lk / AT_BN / 2) & ~1;
   const int blocks = p.nreg + 2 * nsplit;
   if (q_scaled)
     hipLaunchKernelGGL((flash_attn_kernel<T, DH, true, W, 1, AT_BN>), dim3(blocks), dim3(64 * W), 0, stream, p);
@@ -1283,12 +1288,12 @@ void launch_groups(AttnParams<T> p, bool q_scaled, hipStream_t stream) {
 // block, whose keys are not in the L2 yet and which a lone round does not hide.
 template <typename T>
 bool prefer_g2(const AttnParams<T>& p, int ncu) {
-  constexpr int kChip = 256;
-  const float four = (float)(((p.Lq + 127) / 128) * p.H * p.B) / (2 * kChip);
+  const int cus = est_cus(ncu);
+  const float four = (float)(((p.Lq + 127) / 128) * p.H * p.B) / (2 * cus);
   if (p.Lk < 2048 || four <= 1.f) return false;
-  const int items = ((p.Lq + 255) / 256) * p.H * p.B, rem = items % kChip;
-  const bool split = p.part && ncu > 0 && rem > 0 && 2 * rem <= ncu && rem <= kMaxSplitItems;
-  const float rounds = (float)(items / kChip) + (rem == 0 ? 0.f : split ? 0.5f : 1.f);
+  const auto [items, nsplit] = key_split(p, 256, 1, ncu);
+  const bool split = nsplit > 0;
+  const float rounds = (float)(items / cus) + (items % cus == 0 ? 0.f : split ? 0.5f : 1.f);
   const float nt = (float)((p.Lk + 63) / 64);
   return 1.03f * (nt * 1.7f * rounds + (split ? 16.f : 8.f)) < nt * 2.27f * four;
 }
@@ -1303,16 +1308,15 @@ bool prefer_g2(const AttnParams<T>& p, int ncu) {
 // keys (2216 x 8, 24 heads: 40 -> 60).
 template <typename T, int DH>
 bool prefer_groups(const AttnParams<T>& p, int ncu) {
-  constexpr int kChip = 256, occ = DH == 128 ? 1 : 2;
+  constexpr int occ = DH == 128 ? 1 : 2;
   constexpr float per64 = DH == 128 ? 9.f : 4.2f, fixed4 = 8.f, fixed2 = DH == 128 ? 12.f : 10.f;
   auto up = [](int64_t n, int64_t m) { return (float)((n + m - 1) / m); };
-  const int64_t bh = (int64_t)p.B * p.H, items4 = (p.Lq + 127) / 128 * bh, items2 = (p.Lq + 63) / 64 * bh;
-  const int rem = ncu > 0 ? (int)(items4 % (2 * ncu)) : 0;   // (as launch_w splits)
-  const bool split = p.part && rem > 0 && rem <= ncu && rem <= kMaxSplitItems && p.Lk / AT_BN >= 4;
-  const float full = up(items4 - (split ? rem : 0), kChip), half = split ? up(2 * rem, kChip) : 0.f;
+  const int cus = est_cus(ncu);
+  const auto [items4, nsplit] = key_split(p, 128, 2, ncu);   // (as launch_w)
+  const float full = up(items4 - nsplit, cus), half = up(2 * nsplit, cus);
   const float t4 = (full + 0.5f * half) * up(p.Lk, 64) * per64 +
-                   fixed4 * up((int64_t)(full + half), occ) + (split ? 8.f : 0.f);
-  const float n2 = up(items2, kChip);
+                   fixed4 * up((int64_t)(full + half), occ) + (nsplit > 0 ? 8.f : 0.f);
+  const float n2 = up((int64_t)((p.Lq + 63) / 64) * p.H * p.B, cus);
   const float t2 = n2 * up((p.Lk + 31) / 32, 2) * 0.5f * per64 + fixed2 * up((int64_t)n2, occ);
   return t2 < t4;
 }

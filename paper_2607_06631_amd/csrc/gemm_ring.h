@@ -430,8 +430,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_ring_kernel(GemmPara
 // ---------------------------------------------------------------------------
 // Choice of the tile
 // ---------------------------------------------------------------------------
-constexpr int kCus = 256;
-
 // Tile shapes, largest first.  c1: microseconds per k-tile of a lone workgroup
 // on each CU; cn: the same divided among several per CU; f: fixed cost of a
 // round of tiles (prologue, first loads, epilogue); occ: workgroups a CU

@@ -8,6 +8,12 @@ namespace dif {
 
 typedef __bf16 bf16;
 
+// CUs of the whole chip, which the estimates behind the GEMM tiles, the row
+// splits and the attention kernels were measured on.  (Results do not depend on
+// the count; attention uses the device's own where its caller gives it, since the
+// key split does.)
+constexpr int kCus = 256;
+
 enum Epi { EPI_STORE = 0, EPI_GELU = 1, EPI_RESIDUAL = 2 };
 
 // Optional index-table gather of the B operand from a union weight matrix.

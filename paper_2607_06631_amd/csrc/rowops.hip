@@ -42,8 +42,7 @@ struct RowSplit {
   int waves, rpw;
 };
 inline RowSplit row_split(int64_t rows, int max_waves, int max_rpw) {
-  constexpr int kWorkgroups = 256;
-  const int64_t per = (rows + kWorkgroups - 1) / kWorkgroups;   // rows per workgroup
+  const int64_t per = (rows + kCus - 1) / kCus;   // rows per workgroup
   if (per >= (int64_t)max_waves * max_rpw) return {max_waves, max_rpw};
   if (per >= max_waves) return {max_waves, (int)((per + max_waves - 1) / max_waves)};
   int w = 2;

@@ -95,3 +95,38 @@ def test_keys_whose_scores_overflow_downwards(dh, lo, hi, Lk):
         ref = O.attention(q[:, c].astype(np.float64), k[keep][:, c].astype(np.float64),
                           v[keep][:, c].astype(np.float64), 1, dh)
         assert rel_err(to_np(out)[:, c], ref) <= 1e-5
+
+
+@pytest.mark.parametrize("cus", [32, 64, 128, 250])
+@pytest.mark.parametrize("dtype,H,Lq,Lk", [("bf16", 9, 1300, 2100), ("bf16", 5, 700, 600), ("f32", 5, 700, 600),
+                                           ("bf16", 3, 300, 4200)])
+def test_choice_and_key_split_for_other_cu_counts(dtype, H, Lq, Lk, cus):
+    """The launcher given another CU count than the whole chip's (a partition's):
+    the choice of kernel and the key split are made for that count, with every
+    query in exactly one workgroup or one split pair."""
+    import ctypes as C
+    import torch
+    say(f"attention {dtype} H={H} Lq={Lq} Lk={Lk} for {cus} CUs")
+    g = np.random.default_rng(Lq + Lk)
+    bf, dh = dtype == "bf16", 128
+    tdt, W, ldvt = (torch.bfloat16 if bf else torch.float32), H * dh, -(-Lk // 64) * 64
+    q, k, v = (g.standard_normal((n, W), dtype=np.float32) for n in (Lq, Lk, Lk))
+    if bf:
+        q, k, v = (bf16_round(a) for a in (q, k, v))
+    vt = np.zeros((W, ldvt), np.float32)
+    vt[:, :Lk] = v.T
+    Q, K, Vt = (torch.from_numpy(a).cuda().to(tdt) for a in (q, k, vt))
+    out = torch.full_like(Q, float("nan"))
+    ws = torch.empty(B.dif_attention_split_bytes(dh), dtype=torch.uint8, device="cuda")
+    f = getattr(B.lib(), "_ZN3dif16launch_attentionI%sEE10hipError_tiPKT_lS4_lS4_lPS2_liiiiP12ihipStream_tbPfi"
+                         % ("DF16b" if bf else "f"))
+    f.restype = C.c_int
+    f.argtypes = ([C.c_int] + [C.c_void_p, C.c_int64] * 4 + [C.c_int] * 4
+                  + [C.c_void_p, C.c_bool, C.c_void_p, C.c_int])
+    assert f(dh, Q.data_ptr(), W, K.data_ptr(), W, Vt.data_ptr(), ldvt, out.data_ptr(), W, 1, Lq, Lk, H,
+             torch.cuda.current_stream().cuda_stream, False, ws.data_ptr(), cus) == 0
+    torch.cuda.synchronize()
+    for h in range(H):
+        c = slice(h * dh, (h + 1) * dh)
+        ref = O.attention(q[:, c].astype(np.float64), k[:, c].astype(np.float64), v[:, c].astype(np.float64), 1, dh)
+        assert rel_err(to_np(out)[:, c], ref) <= (2e-2 if bf else 1e-5)
