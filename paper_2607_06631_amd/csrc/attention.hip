@@ -37,6 +37,8 @@
 // are ready the one issuing MFMAs wins and the other's softmax VALU work
 // fills the gaps (measured +2%).
 // The kernel fits in 256 registers per lane (two waves per SIMD).
+#include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -1281,11 +1283,14 @@ void launch_groups(AttnParams<T> p, bool q_scaled, hipStream_t stream) {
 // Whether the two-group kernel is the faster one for fewer keys than
 // kLongKeys.  A 64-key tile costs it 1.7 us per round of a workgroup (256
 // queries) on every CU, half a round when the last one is split; the four-wave
-// kernel takes 2.27 us for as many queries, but in steps of 128 queries.  (3600
-// tokens, 40 heads: 263 us split, 294 four-wave, 298 unsplit.)  Only where the
-// four-wave kernel needs more than one round itself: with 27 heads of 1560
-// tokens, 49 against 51 us repeated on the same tensors but 68 against 62 in a
-// block, whose keys are not in the L2 yet and which a lone round does not hide.
+// kernel takes 2.27 us for as many queries, but in steps of 128 queries, and 1.97
+// per round where the last one is nearly full too (33 heads x 2 x 2886: 266 us,
+// two-group 276; 26 x 2 x 3636: 319 and 329).  (3600 tokens, 40 heads: 254 us
+// split, 290 four-wave, 298 unsplit: calls that bring no split workspace, the
+// blocks' below 4096 tokens among them, keep the four-wave kernel there.)  Only
+// where the four-wave kernel needs more than one round itself: with 27 heads of
+// 1560 tokens, 49 against 51 us repeated on the same tensors but 68 against 62 in
+// a block, whose keys are not in the L2 yet and which a lone round does not hide.
 template <typename T>
 bool prefer_g2(const AttnParams<T>& p, int ncu) {
   const int cus = est_cus(ncu);
@@ -1295,7 +1300,8 @@ bool prefer_g2(const AttnParams<T>& p, int ncu) {
   const bool split = nsplit > 0;
   const float rounds = (float)(items / cus) + (items % cus == 0 ? 0.f : split ? 0.5f : 1.f);
   const float nt = (float)((p.Lk + 63) / 64);
-  return 1.03f * (nt * 1.7f * rounds + (split ? 16.f : 8.f)) < nt * 2.27f * four;
+  const float t4 = nt * std::min(2.27f * four, 1.97f * std::ceil(four));
+  return 1.03f * (nt * 1.7f * rounds + (split ? 16.f : 8.f)) < t4;
 }
 
 // float32: whether the key groups are estimated faster than four query groups of
@@ -1305,7 +1311,10 @@ bool prefer_g2(const AttnParams<T>& p, int ncu) {
 // heads, head_dim 128: 164 -> 96 us) or a last round nearly empty (3000 tokens,
 // 12 heads: 789 -> 664), and costs its merge and a second set of tiles where they
 // do not (947 tokens, 64 heads: 271 -> 311) or where there is a tile or two of
-// keys (2216 x 8, 24 heads: 40 -> 60).
+// keys (2216 x 8, 24 heads: 40 -> 60).  With head_dim 128 and more than two rounds
+// the 128-query workgroups overlap theirs (7.5 rounds' time for the 8 of 40 heads
+// x 2 x 2866: 3040 us, in key groups 3197); with head_dim 64, two per CU, the
+// groups gain as much by it (35 heads x 2 x 1485: 382 and 362).
 template <typename T, int DH>
 bool prefer_groups(const AttnParams<T>& p, int ncu) {
   constexpr int occ = DH == 128 ? 1 : 2;
@@ -1314,8 +1323,9 @@ bool prefer_groups(const AttnParams<T>& p, int ncu) {
   const int cus = est_cus(ncu);
   const auto [items4, nsplit] = key_split(p, 128, 2, ncu);   // (as launch_w)
   const float full = up(items4 - nsplit, cus), half = up(2 * nsplit, cus);
-  const float t4 = (full + 0.5f * half) * up(p.Lk, 64) * per64 +
-                   fixed4 * up((int64_t)(full + half), occ) + (nsplit > 0 ? 8.f : 0.f);
+  const float t4 = ((full + 0.5f * half) * up(p.Lk, 64) * per64 +
+                    fixed4 * up((int64_t)(full + half), occ) + (nsplit > 0 ? 8.f : 0.f)) *
+                   (DH == 128 && items4 > 2 * cus ? 0.93f : 1.f);
   const float n2 = up((int64_t)((p.Lq + 63) / 64) * p.H * p.B, cus);
   const float t2 = n2 * up((p.Lk + 31) / 32, 2) * 0.5f * per64 + fixed2 * up((int64_t)n2, occ);
   return t2 < t4;
