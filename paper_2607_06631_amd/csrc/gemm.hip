@@ -415,7 +415,7 @@ constexpr int kMaxKChunks = 8192;
 // gemm_ring.h.
 template <typename T, typename OutT, int EPI, int GA>
 hipError_t launch_tile(const GemmParams<T, OutT>& p, hipStream_t stream) {
-  const int shape = pick_tile<T>(p.M, p.N, p.nseg, p.K);
+  const int shape = pick_tile<T>(p.M, p.N, p.nseg, p.K, EPI);
   if constexpr (sizeof(T) == 2 && GA == GA_NONE) {
     if (shape == TS_256) {
       const int tiles = ((p.M + 255) / 256) * ((p.N + 255) / 256) * p.nseg;

@@ -441,7 +441,8 @@ struct TileShape {
   int bm, bn, occ;
   float c1, cn, f, g;
 };
-enum { TS_256 = 0, TS_224, TS_192, TS_160, TS_128W, TS_96W, TS_128, TS_96, TS_64, TS_64S, TS_32, TS_COUNT };
+enum { TS_256 = 0, TS_224, TS_192, TS_160, TS_128W, TS_96W, TS_128, TS_96, TS_64, TS_64S, TS_32, TS_COUNT,
+       TS_128D /* 128 x 128 in two slots, by a rule of its own */ };
 template <typename T>
 inline const TileShape* tile_shapes() {
   static constexpr TileShape bf[TS_COUNT] = {
@@ -463,11 +464,26 @@ inline const TileShape* tile_shapes() {
 // so the estimate is n tiles' k-loops plus the fixed cost of each round; a
 // chip that is only part full runs its k-tiles faster (higher clock, less L2
 // traffic: 0.75-0.95 of the time at half the CUs).  The choice does not look
-// at the gather mode or the epilogue.
+// at the gather mode, nor at the epilogue but for the short reductions below.
 template <typename T>
-inline int pick_tile(int M, int N, int nseg, int K) {
+inline int pick_tile(int M, int N, int nseg, int K, int epi) {
   const TileShape* ts = tile_shapes<T>();
   const float nk = (float)(K / (128 / (int)sizeof(T)));
+  // Store epilogues of up to eight k-tiles, 3/2 to 2 tiles of 128 x 128 per CU:
+  // these in two ring slots, so that a CU holds two workgroups and one's loads and
+  // stores run under the other's, where one workgroup of a wider tile per CU pays
+  // its prologue and its stores in full (11683 x 528 x 384: 10.5 us, 12.3 on 128 x
+  // 256; 6077 x 1047 x 320: 13.3 and 15.2; 53 problems of 8 to 20 us: 0.93 of the
+  // time, worst 1.03).  With 9 to 14 k-tiles it is 0.94 to 1.06, from 23 on slower.
+  // With fewer tiles only where 96 x 256 does not fit one round either.  With GELU
+  // or the residual the wide tiles stay (742 x 7309 x 128: 22.2 us, 27.7).
+  if (sizeof(T) == 2 && epi == EPI_STORE && nk <= 8.f) {
+    auto count = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn) * nseg; };
+    const int64_t tiles = count(128, 128);
+    const bool many = 2 * tiles > 3 * kCus;
+    const bool fewer = 3 * tiles > 4 * kCus && nk >= 4.f && count(96, 256) > kCus;
+    if (tiles <= 2 * kCus && (many || fewer)) return TS_128D;
+  }
   int best = TS_COUNT - 1;
   float tbest = 0.f;
   for (int i = 0; i < TS_COUNT; ++i) {
@@ -522,6 +538,10 @@ hipError_t launch_ring_shape(int shape, const GemmParams<T, OutT>& p, hipStream_
       case TS_128W: launch_ring_cfg<T, OutT, EPI, GA, 2, 4, 4, 4, 3, 1>(p, s); break;
       case TS_96W: launch_ring_cfg<T, OutT, EPI, GA, 2, 4, 3, 4, 3, 1>(p, s); break;
       case TS_128: launch_ring_cfg<T, OutT, EPI, GA, 2, 2, 4, 4, 4, 2>(p, s); break;
+      case TS_128D:
+        if constexpr (EPI == EPI_STORE) launch_ring_cfg<T, OutT, EPI, GA, 2, 2, 4, 4, 2, 2>(p, s);
+        else return hipErrorInvalidValue;
+        break;
       case TS_96: launch_ring_cfg<T, OutT, EPI, GA, 2, 2, 3, 4, 5, 2>(p, s); break;
       case TS_64: launch_ring_cfg<T, OutT, EPI, GA, 2, 2, 2, 4, 3, 2>(p, s); break;
       case TS_64S: launch_ring_cfg<T, OutT, EPI, GA, 2, 2, 2, 2, 4, 2>(p, s); break;

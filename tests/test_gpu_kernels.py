@@ -105,15 +105,15 @@ def test_gemm_ragged_columns_and_unaligned_rows(dtype, ldc_pad):
         assert np.all(out[:M, N:] == 7.0) and np.all(out[M] == 7.0)
 
 
-@pytest.mark.parametrize("M", [127 * 256 - 7, 127 * 256 + 37])
+@pytest.mark.parametrize("M", [127 * 256 - 7, 256 * 128 - 7, 256 * 128 + 37])
 def test_gemm_store_either_side_of_the_small_problem_tiling(M):
-    """Store-epilogue problems with fewer than 128 tiles of 256 x 256 run as
-    128 x 128 tiles: M = 32505 and 32549 with N = 256 give 127 and 128 large
-    tiles, one on each side of the switch; sampled rows incl. the ragged tail
-    against the float64 product."""
+    """Store-epilogue problems of a short reduction run as 128 x 128 tiles, two
+    workgroups per CU, up to 512 of them: M = 32505, 32761 and 32805 with N = 256
+    give 508, 512 and 514, the last one past the switch; sampled rows incl. the
+    ragged tail against the float64 product."""
     import torch
     N, K = 256, 192
-    say(f"gemm store bf16 M={M} N={N} K={K}: {-(-M // 256) * (N // 256)} tiles of 256 x 256")
+    say(f"gemm store bf16 M={M} N={N} K={K}: {-(-M // 128) * (N // 128)} tiles of 128 x 128")
     g = np.random.default_rng(M)
     a, b = _rand(g, (M, K), 0.5), _rand(g, (N, K), 0.5)
     bias = g.standard_normal(N).astype(np.float32)
