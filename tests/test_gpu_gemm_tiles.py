@@ -1,8 +1,9 @@
 """The GEMM operator over its tile shapes, ragged in every dimension.
 
 The sizes are such that the choice of the tile (least estimated time) takes
-each shape in turn; the first group walks the k-loop's edges (fewer k-tiles
-than ring slots, one more, a whole number of turns, one less) on the smallest.
+most shapes in turn, with plain operands of the output's type; the first group
+walks the k-loop's edges (fewer k-tiles than ring slots, one more, a whole number
+of turns, one less) on the smallest.
 Reference: the float64 product of the same inputs on sampled rows.
 """
 import numpy as np
