@@ -66,7 +66,8 @@ inline size_t esize(int dtype) { return dtype == DIF_BF16 ? 2 : 4; }
 enum ProfKind {
   PK_GEMM_QKV = 0, PK_ATTN_SELF, PK_GEMM_SELF_OUT, PK_GEMM_CROSS_Q, PK_GEMM_CROSS_KV,
   PK_ATTN_CROSS, PK_GEMM_CROSS_OUT, PK_GEMM_FFN1, PK_GEMM_FFN2, PK_NORM, PK_QK_NORM,
-  PK_TRANSPOSE, PK_TIME_EMBED, PK_GEMM_IO, PK_GATHER, PK_ELEMENTWISE
+  PK_TRANSPOSE,   // (no launch: the projections write V transposed; kept for the kinds' numbers)
+  PK_TIME_EMBED, PK_GEMM_IO, PK_GATHER, PK_ELEMENTWISE
 };
 const char* kKindNames[DIF_PROF_KINDS] = {
     "gemm_qkv", "attn_self", "gemm_self_out", "gemm_cross_q", "gemm_cross_kv", "attn_cross",
@@ -573,9 +574,9 @@ dif_status block_impl(const dif_plan* plan, int layer, T* x, const T* ctx, const
   if (a > 0) {
     // q and k go to `big` (row-major, for QK-norm in place); v is written
     // transposed into vt [B, a, ldvt] by the same launch, as attention reads
-    // it.  The v columns start on a GEMM tile: in one B matrix when they are a
-    // multiple of 256 (any even count of 128-wide heads), else as a launch
-    // segment of their own, like q and k.
+    // it.  The v columns start on a GEMM tile: in one B matrix when 2 a is a
+    // multiple of 256 (any count of 128-wide heads, an even one of 64-wide), else
+    // as a launch segment of their own, like q and k.
     const dif::GemmVt vtd{vt, wl.ldvt, 2 * a, a, L};
     dif::GemmGather g = g_self_rows;
     if (ix) {

@@ -47,7 +47,8 @@
 
 namespace dif {
 
-// waves per workgroup: 8 when the keys are long (bf16), 4 for short key
+// From here on bf16 runs the two-group kernel (head_dim 128; below it where
+// prefer_g2 says so) or eight waves per workgroup (64), four for shorter key
 // sequences (the text tokens), where eight waves leave too few workgroups and
 // too few key tiles to amortise each workgroup's prologue
 constexpr int kLongKeys = kAttnLongKeys;

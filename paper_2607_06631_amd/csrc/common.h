@@ -96,10 +96,8 @@ __device__ __forceinline__ int xcd_remap(int bid, int total) {
 // window) hit distinct banks, for row-contiguous writes as well.
 template <int CH>
 __device__ __forceinline__ int swz(int row, int c) {
-  static_assert(CH == 4 || CH == 8 || CH >= 16, "LDS rows of 4, 8 or >= 16 chunks");
-  if constexpr (CH == 4) {   // four rows fill a 256-byte window
-    return c ^ ((row >> 2) & 3);
-  } else if constexpr (CH == 8) {
+  static_assert(CH == 8 || CH >= 16, "LDS rows of 8 or >= 16 chunks");
+  if constexpr (CH == 8) {
     return c ^ ((row & 7) ^ ((row >> 3) & 1));
   } else {
     return c ^ (row & 15);

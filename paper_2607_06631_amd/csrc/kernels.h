@@ -68,7 +68,9 @@ size_t attention_split_bytes(int head_dim);
 // The library's static split workspace on the current device (resolved once
 // per device): its device address and size.
 hipError_t attention_static_scratch(float** ptr, size_t* bytes);
-constexpr int kAttnLongKeys = 4096;   // from this key count on, bf16 attention runs 8 waves
+// From this key count on bf16 attention runs the two-group kernel (head_dim 128)
+// or eight waves (64), and blocks' workspaces hold a split region.
+constexpr int kAttnLongKeys = 4096;
 
 // Row LayerNorm of x [M, D] then
 //   mode 0: y = xhat * (1 + p2 + p3) + (p0 + p1)      (AdaLN; p1/p3 may be null)

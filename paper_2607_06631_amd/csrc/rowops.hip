@@ -15,8 +15,6 @@ namespace dif {
 constexpr int R_THREADS = 256;
 constexpr int R_WAVES = R_THREADS / kWave;
 constexpr int R_MAXC = 16;   // 16-byte chunks per lane per row (D <= 1024 * VEC)
-constexpr int R_RPW = 8;     // rows per wave
-constexpr int R_ROWS = R_WAVES * R_RPW;
 
 // ---------------------------------------------------------------------------
 // LayerNorm (biased variance, eps) + AdaLN modulation or affine.
