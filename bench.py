@@ -42,9 +42,9 @@ ATTN_TRAFFIC = {
     "kernel": "attn_self",
     "workload": "wan14b_480p",
     "sources": ("paper_2607_06631_amd/csrc/attention.hip", "paper_2607_06631_amd/csrc/common.h"),
-    "sha256": "129a2dfc3a0be8d15961747479fc6a1c17050d6ab8b9d832e23b8ae05decd872",
-    "fetch_bytes": 1103481.58203125 * 1024 / 0.500,
-    "write_bytes": 255131.5072265625 * 1024 / 1.000,
+    "sha256": "35605253012dd0b7f3453e4ec029fdffe7eb596f5d2d3ef574839dddb7a169db",
+    "fetch_bytes": 1103483.990625 * 1024 / 0.500,
+    "write_bytes": 255131.5109375 * 1024 / 1.000,
 }
 
 
