@@ -116,9 +116,10 @@ __global__ __launch_bounds__(64 * NORM_WAVES) void norm_kernel(const T* __restri
   constexpr bool AHEAD = MAXC <= 12;
   if (AHEAD && row0 < M) load_row(row0);
   auto ld4 = [](const float* p) { return *reinterpret_cast<const f32x4*>(p); };
-  // (two columns' loads at a time beside a row of 12 chunks: four spilled two
-  // registers, 5120 columns and 390 rows 6.5 us, 6.2 now, 7800 rows 28.8 and 27.4)
-  constexpr int U = MAXC == 12 ? 2 : 4;
+  // (three columns' loads at a time beside a row of 12 chunks: four spilled two
+  // registers; two are as fast on vectors in the L2, but 0.5 us a launch behind on
+  // cold ones with few rows)
+  constexpr int U = MAXC == 12 ? 3 : 4;
   if (vec && mode == 0) {
     stage_columns<U>(D, [&](int n) { return ColVecs<4>{ld4(p0 + n), ld4(p1 + n), ld4(p2 + n), ld4(p3 + n)}; },
                      [&](int n, const ColVecs<4>& v) {
